@@ -41,6 +41,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
@@ -79,8 +80,7 @@ struct KdaLds {
     } slow;
   };
   __bf16 pm[kC * CS];               // P (lower incl. diagonal)
-  __bf16 tm[kC * CS];               // T in bf16
-  float x[2][16 * 17];              // 16-block products of the inversion
+  __bf16 tm[kC * CS];               // T in bf16; the 16-blocks above the diagonal stay zero
   float beta[kC];
   float gc[kD];                     // gamma_C per channel
   float qtot[8][kD];                // per-octet decay products
@@ -104,15 +104,6 @@ __device__ __forceinline__ bf16x8 lds_a_perm(const __bf16* rowp, int base) {
   return cat(*reinterpret_cast<const bf16x4*>(rowp + base), *reinterpret_cast<const bf16x4*>(rowp + base + 8));
 }
 
-// The same from an fp32 row, rounded to bf16.
-__device__ __forceinline__ bf16x8 lds_a_perm_f32(const float* rowp, int base) {
-  const float4 lo = *reinterpret_cast<const float4*>(rowp + base);
-  const float4 hi = *reinterpret_cast<const float4*>(rowp + base + 8);
-  return bf16x8{static_cast<__bf16>(lo.x), static_cast<__bf16>(lo.y), static_cast<__bf16>(lo.z),
-                static_cast<__bf16>(lo.w), static_cast<__bf16>(hi.x), static_cast<__bf16>(hi.y),
-                static_cast<__bf16>(hi.z), static_cast<__bf16>(hi.w)};
-}
-
 // Registers 8kk .. 8kk+7 of an accumulator tile, rounded to bf16: a B operand in permuted order.
 __device__ __forceinline__ bf16x8 acc_to_b(const f32x16& acc, int kk) {
   bf16x8 r;
@@ -123,6 +114,14 @@ __device__ __forceinline__ bf16x8 acc_to_b(const f32x16& acc, int kk) {
 
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
 // Transposing LDS read: within each group of 16 lanes, lane i receives element i%4 of the 8 bytes
@@ -222,6 +221,10 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
         S[ib][reg] = src[int64_t(32 * ib + 8 * (reg >> 2) + 4 * hf + (reg & 3)) * kD];
   }
 
+  // the 16-blocks right of an even diagonal block are read as part of its 32 x 32 block, never written
+  for (int e = tid; e < 2 * 256; e += 256)
+    ls.tm[(32 * (e >> 8) + ((e >> 4) & 15)) * CS + 32 * (e >> 8) + 16 + (e & 15)] = static_cast<__bf16>(0.0f);
+
   RawBlock raw;
   {
     const RawAddr first{int64_t(it.cu), min(kC, it.len)};
@@ -289,11 +292,12 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
     // gamma_t = pre * g, gamma_C / gamma_t = sfx * post (a product of the later decays, no division),
     // and k / gamma_t = (k gamma_C / gamma_t) / gamma_C: one reciprocal per channel
     bool slow[4];
-    float inv_tot[4];
+    float rcp[4];                  // post / gamma_C
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       slow[e] = !(tot[e] >= kFastFloor);
-      inv_tot[e] = slow[e] ? 0.0f : __frcp_rn(tot[e]);
+      post[e] = slow[e] ? 0.0f : post[e];
+      rcp[e] = slow[e] ? 0.0f : post[e] * __frcp_rn(tot[e]);
     }
     {
       __bf16 kb[4][8];
@@ -308,9 +312,9 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
           const float gm = pre[e] * g[i][e];
           vq[e] = static_cast<__bf16>(qf[e] * gm);
           vk[e] = static_cast<__bf16>(kf[e] * gm);
-          const float kbar = slow[e] ? 0.0f : kf[e] * (sfx[i][e] * post[e]);
-          vr[e] = static_cast<__bf16>(kbar * inv_tot[e]);
-          kb[e][i] = static_cast<__bf16>(kbar);
+          const float ks = kf[e] * sfx[i][e];
+          vr[e] = static_cast<__bf16>(ks * rcp[e]);
+          kb[e][i] = static_cast<__bf16>(ks * post[e]);
         }
         *reinterpret_cast<bf16x4*>(&ls.qt[t * QS + 4 * cq]) = vq;
         *reinterpret_cast<bf16x4*>(&ls.kt[t * QS + 4 * cq]) = vk;
@@ -456,130 +460,108 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
 
     // ================= phase 2: T = (I + A)^-1 ==================================================
     if (more) load_raw_kq(raw, k, q, next, tok_stride, head_off, tid);
+    // Each wave owns one 16 x 16 diagonal block and needs no barrier for it: the two 8 x 8 halves by
+    // forward substitution (16 lanes, one column each, its coefficients read before the first step),
+    // then T = D - D (L D) with D the halves' inverses and L the block's lower-left 8 x 8, on fp32
+    // MFMAs.  16 -> 32 is the same product (fp32 MFMAs, one wave per pair), 32 -> 64 runs on bf16 MFMAs
+    // split over the four waves.  A 16x16 accumulator (lane group g holds rows 4g + r) is the B operand
+    // of the next product when its contraction slots are taken in that order.  The phase is a latency
+    // chain, so the steps are few and wide: substitution over all 16 rows and the 16 -> 32 sums on the
+    // VALU took 7,400 of a block's 23,600 cycles (4 x 64-head wave of 4,096 tokens: 588 us, now 510).
     {
-      // diagonal 16 x 16 blocks by forward substitution: wave -> block, lane -> column
-      const int a0 = 16 * wave, jc = lane & 15;
-      float xs[16];
-      // row t + 1 of the block is read while row t is solved
-      float4 rc[4] = {}, rn[4] = {};
-#pragma unroll
-      for (int t = 0; t < 16; ++t) {
-        if (t + 1 < 16) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k)
-            if (4 * k < t + 1) rn[k] = *reinterpret_cast<const float4*>(&ls.a[(a0 + t + 1) * AS + a0 + 4 * k]);
-        }
-        float acc = (t == jc) ? 1.0f : 0.0f;
-#pragma unroll
-        for (int u = 0; u < t; ++u) {
-          const float4 r = rc[u >> 2];
-          const float c = (u & 3) == 0 ? r.x : (u & 3) == 1 ? r.y : (u & 3) == 2 ? r.z : r.w;
-          acc -= c * xs[u];
-        }
-        xs[t] = acc;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) rc[k] = rn[k];
-      }
+      const int a0 = 16 * wave, n16 = lane & 15, g16 = lane >> 4;
+      const float* ab = &ls.a[a0 * AS + a0];
+      float* tb = &ls.tf[a0 * AS + a0];
       if (lane < 16) {
+        const int s8 = lane & 8, jc = lane & 7;
+        float c[8][8], xs[8];
 #pragma unroll
-        for (int t = 0; t < 16; ++t) ls.tf[(a0 + t) * AS + a0 + jc] = xs[t];
-        // the block right of an even diagonal block lies above the diagonal of its 32 x 32 block
-        if ((wave & 1) == 0) {
+        for (int t = 1; t < 8; ++t)
 #pragma unroll
-          for (int t = 0; t < 16; ++t) ls.tf[(a0 + t) * AS + a0 + 16 + jc] = 0.0f;
-        }
+          for (int h = 0; h < 2; ++h)
+            if (4 * h < t) {
+              const float4 x = *reinterpret_cast<const float4*>(&ab[(s8 + t) * AS + s8 + 4 * h]);
+              c[t][4 * h] = x.x;
+              c[t][4 * h + 1] = x.y;
+              c[t][4 * h + 2] = x.z;
+              c[t][4 * h + 3] = x.w;
+            }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) xs[t] = (t == jc) ? 1.0f : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+#pragma unroll
+          for (int t = u + 1; t < 8; ++t) xs[t] -= c[t][u] * xs[u];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) tb[(s8 + t) * AS + s8 + jc] = xs[t];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) tb[(s8 + t) * AS + (8 - s8) + jc] = 0.0f;   // the other half's columns
       }
+      f32x4 lx = f32x4{}, ly = f32x4{};
+      const f32x4 la = *reinterpret_cast<const f32x4*>(&ab[n16 * AS + 4 * g16]);
+      const f32x4 da = *reinterpret_cast<const f32x4*>(&tb[n16 * AS + 4 * g16]);
+      float db[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) db[r] = tb[(4 * g16 + r) * AS + n16];
+      const bool low = n16 >= 8 && g16 < 2;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) lx = mfma_f32(low ? la[r] : 0.0f, db[r], lx);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ly = mfma_f32(da[r], lx[r], ly);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float t = db[r] - ly[r];
+        tb[(4 * g16 + r) * AS + n16] = t;
+        ls.tm[(a0 + 4 * g16 + r) * CS + a0 + n16] = static_cast<__bf16>(t);
+      }
+    }
+    lds_barrier();
+    if (wave & 1) {
+      // 16 -> 32: T_ab = -D_a (A_ab D_b) for (a, b) = (1, 0) and (3, 2)
+      const int a0 = 16 * wave, b0 = a0 - 16, n16 = lane & 15, g16 = lane >> 4;
+      const f32x4 la = *reinterpret_cast<const f32x4*>(&ls.a[(a0 + n16) * AS + b0 + 4 * g16]);
+      const f32x4 da = *reinterpret_cast<const f32x4*>(&ls.tf[(a0 + n16) * AS + a0 + 4 * g16]);
+      float db[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) db[r] = ls.tf[(b0 + 4 * g16 + r) * AS + b0 + n16];
+      f32x4 x = f32x4{}, y = f32x4{};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) x = mfma_f32(la[r], db[r], x);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) y = mfma_f32(da[r], x[r], y);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ls.tm[(a0 + 4 * g16 + r) * CS + b0 + n16] = static_cast<__bf16>(-y[r]);
     }
     lds_barrier();
     {
-      // 16 -> 32: T_ab = -D_a A_ab D_b for (a, b) = (1, 0) and (3, 2); two elements per thread
-      const int which = tid >> 7, e = tid & 127, tr = e >> 3, jc = 2 * (e & 7);
-      const int ba = 2 * which + 1, bb = 2 * which;
-      float x0 = 0.0f, x1 = 0.0f;
-      {
-        // all sixteen (A, D) pairs are read before the sums start
-        float av[16];
-        float2 d[16];
+      // 32 -> 64: T21 = -T2 (A21 T1); wave -> 16 columns c0 and 16 rows r0 of T21
+      const int n16 = lane & 15, g16 = lane >> 4, c0 = 16 * (wave & 1), r0 = 16 * (wave >> 1);
+      const __bf16* t1 = &ls.tm[(8 * g16 + (n16 >> 2)) * CS + c0 + 4 * (n16 & 3)];
+      const bf16x8 bop = cat(lds_read_tr(t1), lds_read_tr(t1 + 4 * CS));
+      f32x4 x[2];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float4 a4 = *reinterpret_cast<const float4*>(&ls.a[(16 * ba + tr) * AS + 16 * bb + 4 * k]);
-          av[4 * k] = a4.x;
-          av[4 * k + 1] = a4.y;
-          av[4 * k + 2] = a4.z;
-          av[4 * k + 3] = a4.w;
+      for (int i = 0; i < 2; ++i) {
+        const float* ar = &ls.a[(32 + 16 * i + n16) * AS + 8 * g16];
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(ar), hi = *reinterpret_cast<const f32x4*>(ar + 4);
+        bf16x8 aop;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          aop[e] = static_cast<__bf16>(lo[e]);
+          aop[4 + e] = static_cast<__bf16>(hi[e]);
         }
-#pragma unroll
-        for (int u = 0; u < 16; ++u) d[u] = *reinterpret_cast<const float2*>(&ls.tf[(16 * bb + u) * AS + 16 * bb + jc]);
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          x0 += av[u] * d[u].x;
-          x1 += av[u] * d[u].y;
-        }
+        x[i] = mfma16(aop, bop, f32x4{});
       }
-      ls.x[which][tr * 17 + jc] = x0;
-      ls.x[which][tr * 17 + jc + 1] = x1;
-      lds_barrier();
-      float y0 = 0.0f, y1 = 0.0f;
-      {
-        float dv[16], xa[16], xb[16];
+      const __bf16* t2 = &ls.tm[(32 + r0 + n16) * CS + 32 + 4 * g16];
+      const bf16x8 aop = cat(*reinterpret_cast<const bf16x4*>(t2), *reinterpret_cast<const bf16x4*>(t2 + 16));
+      bf16x8 xb;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float4 d4 = *reinterpret_cast<const float4*>(&ls.tf[(16 * ba + tr) * AS + 16 * ba + 4 * k]);
-          dv[4 * k] = d4.x;
-          dv[4 * k + 1] = d4.y;
-          dv[4 * k + 2] = d4.z;
-          dv[4 * k + 3] = d4.w;
-        }
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          xa[u] = ls.x[which][u * 17 + jc];
-          xb[u] = ls.x[which][u * 17 + jc + 1];
-        }
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-          y0 -= dv[u] * xa[u];
-          y1 -= dv[u] * xb[u];
-        }
+      for (int e = 0; e < 4; ++e) {
+        xb[e] = static_cast<__bf16>(x[0][e]);
+        xb[4 + e] = static_cast<__bf16>(x[1][e]);
       }
-      ls.tf[(16 * ba + tr) * AS + 16 * bb + jc] = y0;
-      ls.tf[(16 * ba + tr) * AS + 16 * bb + jc + 1] = y1;
-    }
-    lds_barrier();
-    if (wave == 0) {
-      // 32 -> 64 on the matrix cores: T21 = -T2 (A21 T1)
-      f32x16 xacc = {};
+      const f32x4 y = mfma16(aop, xb, f32x4{});
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        const float* arow = &ls.a[(32 + col) * AS + 16 * kk + 8 * hf];
-        const float4 lo = *reinterpret_cast<const float4*>(arow), hi = *reinterpret_cast<const float4*>(arow + 4);
-        const bf16x8 aop{static_cast<__bf16>(lo.x), static_cast<__bf16>(lo.y), static_cast<__bf16>(lo.z),
-                         static_cast<__bf16>(lo.w), static_cast<__bf16>(hi.x), static_cast<__bf16>(hi.y),
-                         static_cast<__bf16>(hi.z), static_cast<__bf16>(hi.w)};
-        bf16x8 bop;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) bop[e] = static_cast<__bf16>(ls.tf[(16 * kk + 8 * hf + e) * AS + col]);
-        xacc = mfma(aop, bop, xacc);
-      }
-      f32x16 yacc = {};
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
-        yacc = mfma(lds_a_perm_f32(&ls.tf[(32 + col) * AS + 32], 16 * kk + 4 * hf), acc_to_b(xacc, kk), yacc);
-#pragma unroll
-      for (int reg = 0; reg < 16; ++reg) {
-        const int m = 8 * (reg >> 2) + 4 * hf + (reg & 3);
-        ls.tm[(32 + m) * CS + col] = static_cast<__bf16>(-yacc[reg]);
-      }
-    } else {
-      // diagonal 32-blocks to bf16 (zero above the diagonal 16-blocks): 2 x 32 rows x 4 segments of 8
-      for (int sgi = tid - 64; sgi < 256; sgi += 192) {
-        const int blk32 = sgi >> 7, row = (sgi >> 2) & 31, seg = sgi & 3;
-        const int t = 32 * blk32 + row, s0 = 32 * blk32 + 8 * seg;
-        bf16x8 w;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) w[e] = static_cast<__bf16>(((s0 + e) >> 4) <= (t >> 4) ? ls.tf[t * AS + s0 + e] : 0.0f);
-        *reinterpret_cast<bf16x4*>(&ls.tm[t * CS + s0]) = bf16x4{w[0], w[1], w[2], w[3]};
-        *reinterpret_cast<bf16x4*>(&ls.tm[t * CS + s0 + 4]) = bf16x4{w[4], w[5], w[6], w[7]};
-      }
+      for (int r = 0; r < 4; ++r) ls.tm[(32 + r0 + 4 * g16 + r) * CS + c0 + n16] = static_cast<__bf16>(-y[r]);
     }
     lds_barrier();
 
