@@ -10,6 +10,7 @@ namespace wavepp {
 constexpr uint32_t kMagic = 0x57415650u;   // "WAVP"
 constexpr int kGqaRowsPerItem = 256;       // grouped kernel: 8 waves x 32 query rows
 constexpr int kKvTile = 128;               // grouped kernel: keys per inner-loop tile
+constexpr int kNumCu = 256;                // compute units of the chip: workgroups of a launch that stays resident
 constexpr int kNumXcd = 8;                 // L2 domains a launch is spread over, round-robin
 constexpr int kMlaRowsPerItem = 128;       // latent kernel: query rows per work item
 constexpr int kMlaKvTile = 64;             // latent kernel: keys per tile

@@ -25,14 +25,31 @@
 // and P through an exact pairwise term exp2(G_t - G_s) in log2 space instead, and its Kbar uses
 // exp2(G_C - G_s).
 //
-// Workgroup = one (request, head), 4 waves.  Wave w owns state columns [32w, 32w + 32) as four
-// 32 x 32 fp32 accumulator tiles.  The accumulator layout of v_mfma_f32_32x32x16_bf16 (lane = column,
-// 16 rows per lane) is reused directly as the B operand of the next contraction: the eight rows a lane
-// holds for one MFMA are its contraction slots, and the A operand is read from LDS in that same
-// (permuted) order.
+// Workgroup = 8 waves on one CU, running (request, head) chains one after another, one 64-token block
+// at a time.  The work of a block falls into two parts that different waves run at the same time, one
+// block apart:
+//   * Waves 0-3 (builders) make everything that does not depend on the state, one block ahead: the
+//     decays, the scaled operands, A, P and T.
+//   * Waves 4-7 (runners) carry the state.  Runner w owns state columns [32w, 32w + 32) as four
+//     32 x 32 fp32 accumulator tiles.  The accumulator layout of v_mfma_f32_32x32x16_bf16 (lane =
+//     column, 16 rows per lane) is reused directly as the B operand of the next contraction: the eight
+//     rows a lane holds for one MFMA are its contraction slots, and the A operand is read from LDS in
+//     that same (permuted) order.
+// Every step of either part is a latency chain (LDS round trips, short dependent products), so two
+// waves per SIMD in different parts hide each other's waits.  A period has six workgroup barriers
+// (more with slow channels); both loops below pass each of them once per block built:
+//     barrier      builders (block n + 1)                   runners (block n)
+//     .. 1         octet decay products                     U = T R
+//     .. 2         Q~, K~, K_R, Kbar of the block           O += P U, state update
+//     .. 3         A, P                                     outputs to memory, V of block n + 1 to LDS
+//     .. 4, 5, 6   T in three steps                         K~ S0 and Q~ S0 of block n + 1
+// Q~, K~, P and T are single buffers: a period reads block n's before the barrier after which block
+// n + 1's are written.  Kbar, gamma_C and beta are read later than that and have two.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
+
+#include <algorithm>
 
 namespace wavepp {
 namespace {
@@ -51,10 +68,10 @@ constexpr int kD = kKdaDim;         // d_k = d_v
 // 32 lanes of a half-wave read 8 bytes each from 32 consecutive rows: with a row stride that is an odd
 // multiple of 8 bytes modulo 256 those land on 32 distinct bank pairs.  Arrays read that way keep
 // rows only 8-byte aligned and are accessed 8 bytes at a time.
-constexpr int RS = kD + 8;          // bf16 row stride of K_R and of the staged output (16-byte accesses)
+constexpr int RS = kD + 8;          // bf16 row stride of K_R (16-byte accesses)
 constexpr int QS = kD + 4;          // bf16 row stride of Q~ and K~: 264 B
-constexpr int VS = kD + 32;         // bf16 row stride of V: 320 B, so that the 4 rows x 64 B of a
-                                    // transposing read cover the 64 banks once
+constexpr int VW = 32;              // bf16 row stride of a runner's columns of V: the 4 rows x 64 B of a
+                                    // transposing read are 256 consecutive bytes
 constexpr int CS = kC + 4;          // bf16 row stride of [channel][t] arrays and of P, T [t][s]: 136 B
 constexpr int AS = kC + 4;          // fp32 row stride of A and of T during the inversion
 constexpr int kSlowBatch = 16;      // slow channels staged per pass
@@ -67,10 +84,9 @@ struct KdaLds {
   union {
     __bf16 kr[kC * RS];             // K_R = k / gamma (0 for slow channels)   [t][c]
     float tf[kC * AS];              // T = (I + A)^-1 in fp32 while it is built
-    __bf16 ob[kC * RS];             // the block's output rows, staged for 16-byte stores
   };
-  __bf16 kbt[kD * CS];              // Kbar^T                  [c][t]
-  __bf16 v[kC * VS];                // V                       [t][j]
+  __bf16 kbt[2][kD * CS];           // Kbar^T                  [c][t]
+  __bf16 vo[4][kC * VW];            // per runner: its columns of V [t][j], then of the block's outputs
   union {
     float a[kC * AS];               // A (beta-scaled, strictly lower)
     struct {                        // slow channels of one batch, log2-space
@@ -81,10 +97,11 @@ struct KdaLds {
   };
   __bf16 pm[kC * CS];               // P (lower incl. diagonal)
   __bf16 tm[kC * CS];               // T in bf16; the 16-blocks above the diagonal stay zero
-  float beta[kC];
-  float gc[kD];                     // gamma_C per channel
+  float beta[2][kC];
+  float gc[2][kD];                  // gamma_C per channel
   float qtot[8][kD];                // per-octet decay products
   int slow_list[kD];
+  int nslow;
 };
 
 __device__ __forceinline__ bool kda_meta_ok(const KdaDevPlan& p) {
@@ -137,110 +154,106 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const __bf16* p) {
 // operations before the barrier is enough.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Raw inputs of one block, as loaded by one thread: channels 4 cq .. 4 cq + 3 of tokens
-// 8 oc .. 8 oc + 7 (alpha, k, q), 32 values of one token (v) and one beta.
+// Position in a workgroup's run: block [blk, blk + 64) of one (request, head) chain.  Workgroup w of G
+// takes chains w, 2G - 1 - w, 2G + w, ... of the list (longest chunks first), so that the loads even out.
+struct Cursor {
+  int round = 0, blk = 0, head = 0;
+  int cu = 0, len = 0, state_in = -1, state_out = -1;   // of the chain's item
+  bool valid = false;
+
+  __device__ __forceinline__ void open(const KdaDevPlan& p) {
+    const int G = gridDim.x;
+    const int c = round * G + ((round & 1) ? G - 1 - int(blockIdx.x) : int(blockIdx.x));
+    valid = c < p.num_items * p.num_heads;
+    if (!valid) return;
+    const int item = c / p.num_heads;
+    head = c - item * p.num_heads;
+    // scalar loads: the metadata is never written by this kernel
+    const auto* it = (const __attribute__((address_space(4))) KdaItem*)(p.items + item);
+    cu = it->cu;
+    len = it->len;
+    state_in = it->state_in;
+    state_out = it->state_out;
+    blk = 0;
+  }
+  __device__ __forceinline__ bool last() const { return blk + kC >= len; }
+  __device__ __forceinline__ void advance(const KdaDevPlan& p) {
+    if (last()) {
+      ++round;
+      open(p);
+    } else {
+      blk += kC;
+    }
+  }
+  __device__ __forceinline__ int rows() const { return min(kC, len - blk); }
+  __device__ __forceinline__ int64_t tok0() const { return int64_t(cu) + blk; }
+};
+
+// Raw inputs of one block, as loaded by one builder thread: channels 4 cq .. 4 cq + 3 of tokens
+// 8 oc .. 8 oc + 7 (alpha, k, q) and one beta.  Rows past the block's last token re-read its last row
+// (always in bounds) and are replaced by neutral values (alpha = 1, k = q = 0, beta = 0) when they are
+// consumed.  The next block's inputs are loaded in two groups spread over the current block, so that no
+// single burst fills the memory request queue and stalls the issuing wave.
 struct RawBlock {
   float4 a[8];
   uint2 k[8], q[8];
-  uint4 v[4];
   float b;
 };
 
-// The next block's inputs are loaded in three groups spread over the current block (alpha; k and q;
-// v and beta), so that no single burst fills the memory request queue and stalls the issuing wave.
-// Rows past the block's last token re-read its last row (always in bounds) and are replaced by
-// neutral values (alpha = 1, k = q = v = 0, beta = 0) when they are consumed: no branches here.
-struct RawAddr {
-  int64_t tok0;
-  int L;
-};
-
-__device__ __forceinline__ void load_raw_alpha(RawBlock& r, const float* __restrict__ alpha, RawAddr a,
-                                               int64_t tok_stride, int64_t head_off, int tid) {
-  const int cq = tid & 31, oc = tid >> 5;
+__device__ __forceinline__ void load_raw_alpha(RawBlock& r, const float* __restrict__ alpha, const Cursor& c,
+                                               int64_t tok_stride, int tid) {
+  const int cq = tid & 31, oc = tid >> 5, L = c.rows();
+  const float* src = alpha + (c.tok0() + min(8 * oc, L - 1)) * tok_stride + int64_t(c.head) * kD + 4 * cq;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const int t = min(8 * oc + i, a.L - 1);
-    r.a[i] = *reinterpret_cast<const float4*>(alpha + (a.tok0 + t) * tok_stride + head_off + 4 * cq);
+    r.a[i] = *reinterpret_cast<const float4*>(src);
+    src += 8 * oc + i + 1 < L ? tok_stride : 0;
   }
 }
 
-__device__ __forceinline__ void load_raw_kq(RawBlock& r, const __bf16* __restrict__ k, const __bf16* __restrict__ q,
-                                            RawAddr a, int64_t tok_stride, int64_t head_off, int tid) {
-  const int cq = tid & 31, oc = tid >> 5;
+__device__ __forceinline__ void load_raw_kqb(RawBlock& r, const __bf16* __restrict__ k, const __bf16* __restrict__ q,
+                                             const float* __restrict__ beta, const Cursor& c, int64_t tok_stride, int H,
+                                             int tid) {
+  const int cq = tid & 31, oc = tid >> 5, L = c.rows();
+  int64_t at = (c.tok0() + min(8 * oc, L - 1)) * tok_stride + int64_t(c.head) * kD + 4 * cq;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const int t = min(8 * oc + i, a.L - 1);
-    const int64_t base = (a.tok0 + t) * tok_stride + head_off + 4 * cq;
-    r.k[i] = *reinterpret_cast<const uint2*>(k + base);
-    r.q[i] = *reinterpret_cast<const uint2*>(q + base);
+    r.k[i] = *reinterpret_cast<const uint2*>(k + at);
+    r.q[i] = *reinterpret_cast<const uint2*>(q + at);
+    at += 8 * oc + i + 1 < L ? tok_stride : 0;
   }
+  r.b = beta[(c.tok0() + min(tid & 63, L - 1)) * H + c.head];
 }
 
-__device__ __forceinline__ void load_raw_vb(RawBlock& r, const __bf16* __restrict__ v, const float* __restrict__ beta,
-                                            RawAddr a, int64_t tok_stride, int64_t head_off, int head, int H, int tid) {
-  const int tv = min(tid >> 2, a.L - 1), part = tid & 3;
-  // lane `part` of a row takes its 16-byte chunks part + 4u: the four lanes of a row read (and later
-  // write to LDS) 64 contiguous bytes per u
-  const uint4* src = reinterpret_cast<const uint4*>(v + (a.tok0 + tv) * tok_stride + head_off + 8 * part);
-#pragma unroll
-  for (int u = 0; u < 4; ++u) r.v[u] = src[4 * u];
-  r.b = beta[(a.tok0 + min(tid, a.L - 1)) * H + head];
-}
+// LDS row that holds output row t: rows 4 apart, which the two half-waves write together, would
+// otherwise start on the same bank.
+__device__ __forceinline__ int out_row(int t) { return t ^ ((t >> 2) & 1); }
 
-__global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const __bf16* __restrict__ q,
-                                                             const __bf16* __restrict__ k,
-                                                             const __bf16* __restrict__ v,
-                                                             const float* __restrict__ alpha,
-                                                             const float* __restrict__ beta,
-                                                             float* __restrict__ state_pool,
-                                                             __bf16* __restrict__ out) {
-  __shared__ __attribute__((aligned(16))) KdaLds ls;
-  if (!kda_meta_ok(p)) return;
+__device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, const __bf16* __restrict__ q,
+                                             const __bf16* __restrict__ k, const float* __restrict__ alpha,
+                                             const float* __restrict__ beta, int wave, int tid) {
+  const int lane = tid & 63, col = lane & 31, hf = lane >> 5;
   const int H = p.num_heads;
-  const int item_idx = blockIdx.x / H, head = blockIdx.x - item_idx * H;
-  if (item_idx >= p.num_items) return;
-  const KdaItem it = p.items[item_idx];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, col = lane & 31, hf = lane >> 5;
   const int64_t tok_stride = int64_t(H) * kD;           // elements between tokens of one head
-  const int64_t head_off = int64_t(head) * kD;
-  const int j0 = 32 * wave;                             // this wave's state columns
-  const int cq = tid & 31, oc = tid >> 5;               // phase 0: channels 4 cq + e, tokens 8 oc + i
-
-  // ---- state S0 (fp32) -------------------------------------------------------------------------
-  // tile ib, register 4b + r: row i = 32 ib + 8 b + 4 hf + r, column j0 + col
-  f32x16 S[4];
-#pragma unroll
-  for (int ib = 0; ib < 4; ++ib) S[ib] = f32x16{};
-  if (it.state_in >= 0) {
-    const float* src = state_pool + (int64_t(it.state_in) * H + head) * kD * kD + j0 + col;
-#pragma unroll
-    for (int ib = 0; ib < 4; ++ib)
-#pragma unroll
-      for (int reg = 0; reg < 16; ++reg)
-        S[ib][reg] = src[int64_t(32 * ib + 8 * (reg >> 2) + 4 * hf + (reg & 3)) * kD];
-  }
-
-  // the 16-blocks right of an even diagonal block are read as part of its 32 x 32 block, never written
-  for (int e = tid; e < 2 * 256; e += 256)
-    ls.tm[(32 * (e >> 8) + ((e >> 4) & 15)) * CS + 32 * (e >> 8) + 16 + (e & 15)] = static_cast<__bf16>(0.0f);
-
+  const int cq = tid & 31, oc = tid >> 5;               // channels 4 cq + e, tokens 8 oc + i
+  Cursor cur;
+  cur.open(p);
   RawBlock raw;
-  {
-    const RawAddr first{int64_t(it.cu), min(kC, it.len)};
-    load_raw_alpha(raw, alpha, first, tok_stride, head_off, tid);
-    load_raw_kq(raw, k, q, first, tok_stride, head_off, tid);
-    load_raw_vb(raw, v, beta, first, tok_stride, head_off, head, H, tid);
+  if (cur.valid) {
+    load_raw_alpha(raw, alpha, cur, tok_stride, tid);
+    load_raw_kqb(raw, k, q, beta, cur, tok_stride, H, tid);
   }
+  for (int buf = 0; cur.valid; buf ^= 1) {
+    const int L = cur.rows();
+    const int64_t tok0 = cur.tok0();
+    const int64_t head_off = int64_t(cur.head) * kD;
+    Cursor nxt = cur;
+    nxt.advance(p);
 
-  for (int blk = 0; blk < it.len; blk += kC) {
-    const int L = min(kC, it.len - blk);
-    const int64_t tok0 = int64_t(it.cu) + blk;
-
-    // ================= phase 0: decays, scaled operands, V, beta ================================
+    // ---- decays -------------------------------------------------------------------------------
     float g[8][4];                 // running decay product within the octet, inclusive
     float sfx[8][4];               // decay product of the later tokens of the octet, exclusive
-    {
+    if (L < kC) {
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         if (8 * oc + i >= L) {     // rows past the end: neutral
@@ -248,6 +261,8 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
           raw.k[i] = make_uint2(0, 0);
           raw.q[i] = make_uint2(0, 0);
         }
+    }
+    {
       float run[4] = {1.0f, 1.0f, 1.0f, 1.0f}, back[4] = {1.0f, 1.0f, 1.0f, 1.0f};
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -262,15 +277,11 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
         }
       }
       *reinterpret_cast<float4*>(&ls.qtot[oc][4 * cq]) = make_float4(run[0], run[1], run[2], run[3]);
-      const int tv = tid >> 2, part = tid & 3;
-      const bool vok = tv < L;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        *reinterpret_cast<uint4*>(&ls.v[tv * VS + 8 * part + 32 * u]) = vok ? raw.v[u] : make_uint4(0, 0, 0, 0);
-      if (tid < kC) ls.beta[tid] = tid < L ? raw.b : 0.0f;
+      if (tid < kC) ls.beta[buf][tid] = tid < L ? raw.b : 0.0f;
     }
-    lds_barrier();
+    lds_barrier();   // 1
 
+    // ---- scaled operands ----------------------------------------------------------------------
     float tot[4], pre[4], post[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -322,11 +333,11 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        __bf16* kp = &ls.kbt[(4 * cq + e) * CS + 8 * oc];
+        __bf16* kp = &ls.kbt[buf][(4 * cq + e) * CS + 8 * oc];
         *reinterpret_cast<bf16x4*>(kp) = bf16x4{kb[e][0], kb[e][1], kb[e][2], kb[e][3]};
         *reinterpret_cast<bf16x4*>(kp + 4) = bf16x4{kb[e][4], kb[e][5], kb[e][6], kb[e][7]};
       }
-      if (oc == 0) *reinterpret_cast<float4*>(&ls.gc[4 * cq]) = make_float4(tot[0], tot[1], tot[2], tot[3]);
+      if (oc == 0) *reinterpret_cast<float4*>(&ls.gc[buf][4 * cq]) = make_float4(tot[0], tot[1], tot[2], tot[3]);
     }
     // compact list of the slow channels, in channel order (lanes 0-31 of every wave see all channels)
     int nslow = 0;
@@ -339,6 +350,7 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
         below += __popcll(b & lo32);
         nslow += __popcll(b);
       }
+      if (tid == 0) ls.nslow = nslow;
       if (wave == 0 && lane < 32) {
         int idx = below;
 #pragma unroll
@@ -346,13 +358,10 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
           if (slow[e]) ls.slow_list[idx++] = 4 * cq + e;
       }
     }
-    lds_barrier();
+    lds_barrier();   // 2
 
-    // ================= phase 1: A and P (waves 0-2: tiles (0,0), (1,0), (1,1)) ====================
-    // the next block's inputs arrive while this block is computed (first group here)
-    const bool more = blk + kC < it.len;
-    const RawAddr next{tok0 + kC, min(kC, it.len - blk - kC)};
-    if (more) load_raw_alpha(raw, alpha, next, tok_stride, head_off, tid);
+    // ---- A and P (waves 0-2: tiles (0,0), (1,0), (1,1)) ------------------------------------------
+    if (nxt.valid) load_raw_alpha(raw, alpha, nxt, tok_stride, tid);
     const int tb1 = wave == 0 ? 0 : 1, sb1 = wave == 2 ? 1 : 0;
     f32x16 accA = {}, accP = {};
     if (wave < 3) {
@@ -420,7 +429,7 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int t = 4 * tg + u;
-          ls.kbt[ch * CS + t] = static_cast<__bf16>(ls.slow.k[cl][t] * exp2f(gC - ls.slow.g[cl][t]));
+          ls.kbt[buf][ch * CS + t] = static_cast<__bf16>(ls.slow.k[cl][t] * exp2f(gC - ls.slow.g[cl][t]));
         }
       }
       if (wave < 3) {
@@ -443,7 +452,7 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
       const int s = 32 * sb1 + col;
       float4 btv[4];
 #pragma unroll
-      for (int b = 0; b < 4; ++b) btv[b] = *reinterpret_cast<const float4*>(&ls.beta[32 * tb1 + 8 * b + 4 * hf]);
+      for (int b = 0; b < 4; ++b) btv[b] = *reinterpret_cast<const float4*>(&ls.beta[buf][32 * tb1 + 8 * b + 4 * hf]);
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
         const int t0 = 32 * tb1 + 8 * b + 4 * hf;
@@ -456,10 +465,10 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
         }
       }
     }
-    lds_barrier();
+    lds_barrier();   // 3
 
-    // ================= phase 2: T = (I + A)^-1 ==================================================
-    if (more) load_raw_kq(raw, k, q, next, tok_stride, head_off, tid);
+    // ---- T = (I + A)^-1 -----------------------------------------------------------------------
+    if (nxt.valid) load_raw_kqb(raw, k, q, beta, nxt, tok_stride, H, tid);
     // Each wave owns one 16 x 16 diagonal block and needs no barrier for it: the two 8 x 8 halves by
     // forward substitution (16 lanes, one column each, its coefficients read before the first step),
     // then T = D - D (L D) with D the halves' inverses and L the block's lower-left 8 x 8, on fp32
@@ -515,7 +524,7 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
         ls.tm[(a0 + 4 * g16 + r) * CS + a0 + n16] = static_cast<__bf16>(t);
       }
     }
-    lds_barrier();
+    lds_barrier();   // 4
     if (wave & 1) {
       // 16 -> 32: T_ab = -D_a (A_ab D_b) for (a, b) = (1, 0) and (3, 2)
       const int a0 = 16 * wave, b0 = a0 - 16, n16 = lane & 15, g16 = lane >> 4;
@@ -532,7 +541,7 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
 #pragma unroll
       for (int r = 0; r < 4; ++r) ls.tm[(a0 + 4 * g16 + r) * CS + b0 + n16] = static_cast<__bf16>(-y[r]);
     }
-    lds_barrier();
+    lds_barrier();   // 5
     {
       // 32 -> 64: T21 = -T2 (A21 T1); wave -> 16 columns c0 and 16 rows r0 of T21
       const int n16 = lane & 15, g16 = lane >> 4, c0 = 16 * (wave & 1), r0 = 16 * (wave >> 1);
@@ -563,43 +572,37 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
 #pragma unroll
       for (int r = 0; r < 4; ++r) ls.tm[(32 + r0 + 4 * g16 + r) * CS + c0 + n16] = static_cast<__bf16>(-y[r]);
     }
-    lds_barrier();
+    lds_barrier();   // 6
+    cur = nxt;
+  }
+}
 
-    // ================= phase 3: the state chain (wave -> 32 state columns) =======================
-    if (more) load_raw_vb(raw, v, beta, next, tok_stride, head_off, head, H, tid);
-    {
-      bf16x8 sB[4][2];
+__device__ __forceinline__ void run_blocks(const KdaDevPlan& p, KdaLds& ls, const __bf16* __restrict__ v,
+                                           float* __restrict__ state_pool, __bf16* __restrict__ out, int wave, int lane) {
+  const int col = lane & 31, hf = lane >> 5;
+  const int H = p.num_heads;
+  const int64_t tok_stride = int64_t(H) * kD;
+  const int j0 = 32 * wave;                             // this wave's state columns
+  const int mrow = lane >> 2, mpart = 8 * (lane & 3);   // 16-byte moves of V and O: rows mrow + 16 i
+  __bf16* vo = ls.vo[wave];
+  Cursor cur, nxt;
+  nxt.open(p);
+  // state tile ib, register 4b + r: row i = 32 ib + 8 b + 4 hf + r, column j0 + col
+  f32x16 S[4], accE[2], accO[2];
+  bf16x8 uB[2][2];
+  for (int buf = 1;; buf ^= 1) {   // block n has buffer buf, block n + 1 the other; the first pass has no block n
+    uint4 vraw[4];
+    if (nxt.valid) {
 #pragma unroll
-      for (int ib = 0; ib < 4; ++ib) {
-        sB[ib][0] = acc_to_b(S[ib], 0);
-        sB[ib][1] = acc_to_b(S[ib], 1);
-      }
-      f32x16 accE[2] = {}, accO[2] = {};
-      {
-        // software-pipelined: the A operands of step n + 1 are read while step n's MFMAs run
-        bf16x8 ak = lds_a_perm(&ls.kt[col * QS], 4 * hf);
-        bf16x8 aq = lds_a_perm(&ls.qt[col * QS], 4 * hf);
-#pragma unroll
-        for (int n = 0; n < 16; ++n) {
-          const int ib = n >> 2, kk = (n >> 1) & 1, tb = n & 1;
-          bf16x8 nk = ak, nq = aq;
-          if (n + 1 < 16) {
-            const int m = n + 1;
-            const int cb = 32 * (m >> 2) + 16 * ((m >> 1) & 1) + 4 * hf;
-            nk = lds_a_perm(&ls.kt[(32 * (m & 1) + col) * QS], cb);
-            nq = lds_a_perm(&ls.qt[(32 * (m & 1) + col) * QS], cb);
-          }
-          accE[tb] = mfma(ak, sB[ib][kk], accE[tb]);
-          accO[tb] = mfma(aq, sB[ib][kk], accO[tb]);
-          ak = nk;
-          aq = nq;
-        }
-      }
+      for (int i = 0; i < 4; ++i)
+        vraw[i] = *reinterpret_cast<const uint4*>(v + (nxt.tok0() + min(mrow + 16 * i, nxt.rows() - 1)) * tok_stride +
+                                                  int64_t(nxt.head) * kD + j0 + mpart);
+    }
+    if (cur.valid) {
       // R = beta (V - E), in place in accE.  V[t0 + r][j] for r = 0..3 comes from the transposing
       // read: lane 4m + g of each 16-lane group addresses row t0 + m at column 4g of its group.
-      const int j = j0 + col;
       const int grp = lane >> 4, li = lane & 15;
-      const int jg = j0 + 16 * (grp & 1) + 4 * (li & 3);
+      const int jg = 16 * (grp & 1) + 4 * (li & 3);
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb) {
         // the four V fragments and betas of a block row are read before any is used
@@ -608,8 +611,8 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           const int t0 = 32 * tb + 8 * b + 4 * hf;
-          vv[b] = lds_read_tr(&ls.v[(t0 + (li >> 2)) * VS + jg]);
-          bt[b] = *reinterpret_cast<const float4*>(&ls.beta[t0]);
+          vv[b] = lds_read_tr(&vo[(t0 + (li >> 2)) * VW + jg]);
+          bt[b] = *reinterpret_cast<const float4*>(&ls.beta[buf][t0]);
         }
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
@@ -643,13 +646,15 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
           a = na;
         }
       }
-      bf16x8 uB[2][2];
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb) {
         uB[tb][0] = acc_to_b(accU[tb], 0);
         uB[tb][1] = acc_to_b(accU[tb], 1);
       }
-      // O += P U, then store the valid rows
+    }
+    if (nxt.valid) lds_barrier();   // 1
+    if (cur.valid) {
+      // O += P U; the outputs go to LDS over V, rows 4 apart on distinct banks (out_row)
       {
         bf16x8 a = lds_a_perm(&ls.pm[col * CS], 4 * hf);
 #pragma unroll
@@ -669,17 +674,17 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
 #pragma unroll
         for (int reg = 0; reg < 16; ++reg) {
           const int t = 32 * tb + 8 * (reg >> 2) + 4 * hf + (reg & 3);
-          ls.ob[t * RS + j] = static_cast<__bf16>(accO[tb][reg]);
+          vo[out_row(t) * VW + col] = static_cast<__bf16>(accO[tb][reg]);
         }
       }
       // S = Diag(gamma_C) S + Kbar^T U: 16 products in the order (ib, sb, kk), each A operand read
       // while the previous product runs
       {
-        bf16x8 a = lds_a_perm(&ls.kbt[col * CS], 4 * hf);
+        bf16x8 a = lds_a_perm(&ls.kbt[buf][col * CS], 4 * hf);
         // the decays of block row ib + 1 are read while block row ib is updated
         float4 gcur[4], gnxt[4];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) gcur[b] = *reinterpret_cast<const float4*>(&ls.gc[8 * b + 4 * hf]);
+        for (int b = 0; b < 4; ++b) gcur[b] = *reinterpret_cast<const float4*>(&ls.gc[buf][8 * b + 4 * hf]);
 #pragma unroll
         for (int n = 0; n < 16; ++n) {
           const int ib = n >> 2, sb = (n >> 1) & 1, kk = n & 1;
@@ -687,7 +692,7 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
             if (ib + 1 < 4) {
 #pragma unroll
               for (int b = 0; b < 4; ++b)
-                gnxt[b] = *reinterpret_cast<const float4*>(&ls.gc[32 * (ib + 1) + 8 * b + 4 * hf]);
+                gnxt[b] = *reinterpret_cast<const float4*>(&ls.gc[buf][32 * (ib + 1) + 8 * b + 4 * hf]);
             }
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
@@ -701,46 +706,108 @@ __global__ __launch_bounds__(256, 1) void kda_prefill_kernel(KdaDevPlan p, const
           bf16x8 na = a;
           if (n + 1 < 16) {
             const int m = n + 1;
-            na = lds_a_perm(&ls.kbt[(32 * (m >> 2) + col) * CS], 32 * ((m >> 1) & 1) + 16 * (m & 1) + 4 * hf);
+            na = lds_a_perm(&ls.kbt[buf][(32 * (m >> 2) + col) * CS], 32 * ((m >> 1) & 1) + 16 * (m & 1) + 4 * hf);
           }
           S[ib] = mfma(a, uB[sb][kk], S[ib]);
           a = na;
         }
       }
     }
-    lds_barrier();
-    // the block's output rows leave from LDS as 16-byte stores (the next block writes this storage
-    // only after its first barrier)
-    {
-      const int t = tid >> 2, part = tid & 3;
-      if (t < L) {
-        uint4* dst = reinterpret_cast<uint4*>(out + (tok0 + t) * tok_stride + head_off + 32 * part);
+    if (nxt.valid) {
+      lds_barrier();   // 2
+      const int slow = ls.nslow;
+      for (int base = 0; base < slow; base += kSlowBatch)
+        for (int i = 0; i < 3; ++i) lds_barrier();
+      if (slow > 0) lds_barrier();
+    }
+    if (cur.valid) {
+      const int L = cur.rows();
+      __bf16* dst = out + cur.tok0() * tok_stride + int64_t(cur.head) * kD + j0 + mpart;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) dst[u] = *reinterpret_cast<const uint4*>(&ls.ob[t * RS + 32 * part + 8 * u]);
+      for (int i = 0; i < 4; ++i) {
+        const int t = mrow + 16 * i;
+        if (t < L) *reinterpret_cast<uint4*>(dst + t * tok_stride) = *reinterpret_cast<const uint4*>(&vo[out_row(t) * VW + mpart]);
+      }
+      if (cur.last()) {            // snapshot at the chunk boundary
+        float* st = state_pool + (int64_t(cur.state_out) * H + cur.head) * kD * kD + j0 + col;
+#pragma unroll
+        for (int ib = 0; ib < 4; ++ib)
+#pragma unroll
+          for (int reg = 0; reg < 16; ++reg) st[(32 * ib + 8 * (reg >> 2) + 4 * hf + (reg & 3)) * kD] = S[ib][reg];
       }
     }
-  }
-
-  // ---- snapshot at the chunk boundary ---------------------------------------------------------
-  {
-    float* dst = state_pool + (int64_t(it.state_out) * H + head) * kD * kD + j0 + col;
+    if (!nxt.valid) break;
+    if (nxt.blk == 0) {
 #pragma unroll
-    for (int ib = 0; ib < 4; ++ib)
+      for (int ib = 0; ib < 4; ++ib) S[ib] = f32x16{};
+      if (nxt.state_in >= 0) {
+        const float* st = state_pool + (int64_t(nxt.state_in) * H + nxt.head) * kD * kD + j0 + col;
 #pragma unroll
-      for (int reg = 0; reg < 16; ++reg) {
-        const int i = 32 * ib + 8 * (reg >> 2) + 4 * hf + (reg & 3);
-        dst[int64_t(i) * kD] = S[ib][reg];
+        for (int ib = 0; ib < 4; ++ib)
+#pragma unroll
+          for (int reg = 0; reg < 16; ++reg) S[ib][reg] = st[(32 * ib + 8 * (reg >> 2) + 4 * hf + (reg & 3)) * kD];
       }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<uint4*>(&vo[(mrow + 16 * i) * VW + mpart]) = mrow + 16 * i < nxt.rows() ? vraw[i] : make_uint4(0, 0, 0, 0);
+    // E = K~ S0 and O = Q~ S0, one step of the contraction ahead of the products; barriers 3 to 6 fall
+    // between its steps about where the builders reach them
+    accE[0] = accE[1] = accO[0] = accO[1] = f32x16{};
+    {
+      bf16x8 sB[2];
+      bf16x8 ak = lds_a_perm(&ls.kt[col * QS], 4 * hf);
+      bf16x8 aq = lds_a_perm(&ls.qt[col * QS], 4 * hf);
+#pragma unroll
+      for (int n = 0; n < 16; ++n) {
+        const int ib = n >> 2, kk = (n >> 1) & 1, tb = n & 1;
+        if (tb == 0) sB[kk] = acc_to_b(S[ib], kk);
+        bf16x8 nk = ak, nq = aq;
+        if (n + 1 < 16) {
+          const int m = n + 1;
+          const int cb = 32 * (m >> 2) + 16 * ((m >> 1) & 1) + 4 * hf;
+          nk = lds_a_perm(&ls.kt[(32 * (m & 1) + col) * QS], cb);
+          nq = lds_a_perm(&ls.qt[(32 * (m & 1) + col) * QS], cb);
+        }
+        accE[tb] = mfma(ak, sB[kk], accE[tb]);
+        accO[tb] = mfma(aq, sB[kk], accO[tb]);
+        ak = nk;
+        aq = nq;
+        if (n == 3 || n == 8 || n == 11 || n == 15) lds_barrier();   // 3, 4, 5, 6
+      }
+    }
+    cur = nxt;
+    nxt.advance(p);
   }
 }
 
+__global__ __launch_bounds__(512, 2) void kda_prefill_kernel(KdaDevPlan p, const __bf16* __restrict__ q,
+                                                             const __bf16* __restrict__ k,
+                                                             const __bf16* __restrict__ v,
+                                                             const float* __restrict__ alpha,
+                                                             const float* __restrict__ beta,
+                                                             float* __restrict__ state_pool,
+                                                             __bf16* __restrict__ out) {
+  __shared__ __attribute__((aligned(16))) KdaLds ls;
+  if (!kda_meta_ok(p)) return;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // the 16-blocks right of an even diagonal block are read as part of its 32 x 32 block, never written
+  if (tid < 256)
+    for (int h = 0; h < 2; ++h)
+      ls.tm[(32 * h + (tid >> 4)) * CS + 32 * h + 16 + (tid & 15)] = static_cast<__bf16>(0.0f);
+  // (ordered before their first reader by the period's barriers)
+  if (wave < 4)
+    build_blocks(p, ls, q, k, alpha, beta, wave, tid);
+  else
+    run_blocks(p, ls, v, state_pool, out, wave - 4, tid & 63);
+}
 
 }  // namespace
 
 hipError_t launch_kda_prefill(const KdaDevPlan& p, const void* q, const void* k, const void* v, const float* alpha,
                               const float* beta, float* state_pool, void* out, hipStream_t stream) {
   if (p.num_items == 0) return hipSuccess;
-  const dim3 grid(p.num_items * p.num_heads), block(256);
+  const dim3 grid(std::min(p.num_items * p.num_heads, kNumCu)), block(512);
   hipLaunchKernelGGL(kda_prefill_kernel, grid, block, 0, stream, p, static_cast<const __bf16*>(q),
                      static_cast<const __bf16*>(k), static_cast<const __bf16*>(v), alpha, beta, state_pool,
                      static_cast<__bf16*>(out));
