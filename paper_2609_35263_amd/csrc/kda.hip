@@ -39,8 +39,8 @@
 // waves per SIMD in different parts hide each other's waits.  A period has six workgroup barriers
 // (more with slow channels); both loops below pass each of them once per block built:
 //     barrier      builders (block n + 1)                   runners (block n)
-//     .. 1         octet decay products                     U = T R
-//     .. 2         Q~, K~, K_R, Kbar of the block           O += P U, state update
+//     .. 1         octet decay products
+//     .. 2         Q~, K~, K_R, Kbar of the block           U = T R, O += P U, state update
 //     .. 3         A, P                                     outputs to memory, V of block n + 1 to LDS
 //     .. 4, 5, 6   T in three steps                         K~ S0 and Q~ S0 of block n + 1
 // Q~, K~, P and T are single buffers: a period reads block n's before the barrier after which block
@@ -59,6 +59,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
@@ -86,7 +87,7 @@ struct KdaLds {
     float tf[kC * AS];              // T = (I + A)^-1 in fp32 while it is built
   };
   __bf16 kbt[2][kD * CS];           // Kbar^T                  [c][t]
-  __bf16 vo[4][kC * VW];            // per runner: its columns of V [t][j], then of the block's outputs
+  __bf16 vt[4][kC * VW];            // per runner: its columns of V [t][j]
   union {
     float a[kC * AS];               // A (beta-scaled, strictly lower)
     struct {                        // slow channels of one batch, log2-space
@@ -190,44 +191,52 @@ struct Cursor {
 };
 
 // Raw inputs of one block, as loaded by one builder thread: channels 4 cq .. 4 cq + 3 of tokens
-// 8 oc .. 8 oc + 7 (alpha, k, q) and one beta.  Rows past the block's last token re-read its last row
-// (always in bounds) and are replaced by neutral values (alpha = 1, k = q = 0, beta = 0) when they are
-// consumed.  The next block's inputs are loaded in two groups spread over the current block, so that no
-// single burst fills the memory request queue and stalls the issuing wave.
+// 8 oc .. 8 oc + 7 (alpha, k, q) and one beta.  Rows past the block's last token are not read: they keep
+// what the registers held and are replaced by neutral values (alpha = 1, k = q = 0, beta = 0) when they
+// are consumed.  The next block's rows are loaded as this block's are used up, one per step of the
+// operand scaling: it is the phase with the most ALU work, and no burst fills the memory request queue.
 struct RawBlock {
   float4 a[8];
   uint2 k[8], q[8];
   float b;
 };
 
-__device__ __forceinline__ void load_raw_alpha(RawBlock& r, const float* __restrict__ alpha, const Cursor& c,
-                                               int64_t tok_stride, int tid) {
-  const int cq = tid & 31, oc = tid >> 5, L = c.rows();
-  const float* src = alpha + (c.tok0() + min(8 * oc, L - 1)) * tok_stride + int64_t(c.head) * kD + 4 * cq;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    r.a[i] = *reinterpret_cast<const float4*>(src);
-    src += 8 * oc + i + 1 < L ? tok_stride : 0;
-  }
-}
+struct RawLoader {
+  const float* a;
+  const __bf16 *k, *q;
+  const float* b;
+  int rows, brows;               // rows left of this thread's octet, of the block from this thread's beta row on
 
-__device__ __forceinline__ void load_raw_kqb(RawBlock& r, const __bf16* __restrict__ k, const __bf16* __restrict__ q,
-                                             const float* __restrict__ beta, const Cursor& c, int64_t tok_stride, int H,
-                                             int tid) {
-  const int cq = tid & 31, oc = tid >> 5, L = c.rows();
-  int64_t at = (c.tok0() + min(8 * oc, L - 1)) * tok_stride + int64_t(c.head) * kD + 4 * cq;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    r.k[i] = *reinterpret_cast<const uint2*>(k + at);
-    r.q[i] = *reinterpret_cast<const uint2*>(q + at);
-    at += 8 * oc + i + 1 < L ? tok_stride : 0;
+  __device__ __forceinline__ void open(const float* alpha, const __bf16* kp, const __bf16* qp, const float* beta,
+                                       const Cursor& c, int H, int tid) {
+    const int cq = tid & 31, oc = tid >> 5;
+    const int64_t at = (c.tok0() + 8 * oc) * (int64_t(H) * kD) + int64_t(c.head) * kD + 4 * cq;
+    a = alpha + at;
+    k = kp + at;
+    q = qp + at;
+    b = beta + (c.tok0() + (tid & 63)) * H + c.head;
+    rows = c.valid ? c.rows() - 8 * oc : 0;
+    brows = c.valid ? c.rows() - (tid & 63) : 0;
   }
-  r.b = beta[(c.tok0() + min(tid & 63, L - 1)) * H + c.head];
-}
+  __device__ __forceinline__ void row(RawBlock& r, int i, int64_t tok_stride) const {
+    if (i < rows) {
+      r.a[i] = *reinterpret_cast<const float4*>(a + i * tok_stride);
+      r.k[i] = *reinterpret_cast<const uint2*>(k + i * tok_stride);
+      r.q[i] = *reinterpret_cast<const uint2*>(q + i * tok_stride);
+    }
+  }
+  __device__ __forceinline__ void write_strength(RawBlock& r) const {
+    if (brows > 0) r.b = *b;
+  }
+};
 
-// LDS row that holds output row t: rows 4 apart, which the two half-waves write together, would
-// otherwise start on the same bank.
-__device__ __forceinline__ int out_row(int t) { return t ^ ((t >> 2) & 1); }
+// Element (c, t) of Kbar^T in LDS.  A builder thread writes four tokens of channels 4 cq + e, lanes 544
+// bytes apart: the XOR of the 8-byte unit with c / 32 spreads the four lanes that would share a bank pair.
+// A runner's read of 32 consecutive channels sees a constant XOR.
+__device__ __forceinline__ int kbt_at(int c, int t) { return c * CS + (t ^ ((c >> 5) << 2)); }
+
+// Fence for the scheduler: reads, products and stores stay on their side, ALU work may cross.
+__device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0x6); }
 
 __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, const __bf16* __restrict__ q,
                                              const __bf16* __restrict__ k, const float* __restrict__ alpha,
@@ -239,10 +248,11 @@ __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, co
   Cursor cur;
   cur.open(p);
   RawBlock raw;
-  if (cur.valid) {
-    load_raw_alpha(raw, alpha, cur, tok_stride, tid);
-    load_raw_kqb(raw, k, q, beta, cur, tok_stride, H, tid);
-  }
+  RawLoader ld;
+  ld.open(alpha, k, q, beta, cur, H, tid);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) ld.row(raw, i, tok_stride);
+  ld.write_strength(raw);
   for (int buf = 0; cur.valid; buf ^= 1) {
     const int L = cur.rows();
     const int64_t tok0 = cur.tok0();
@@ -282,23 +292,29 @@ __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, co
     lds_barrier();   // 1
 
     // ---- scaled operands ----------------------------------------------------------------------
-    float tot[4], pre[4], post[4];
+    // Products over the octets: every thread forms gamma_C = tot in the same order (the choice of slow
+    // channels has to agree between the waves); pre and post are those before and after its own octet,
+    // the lower or the upper of its wave's two.
+    f32x4 x[8];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      tot[e] = 1.0f;
-      pre[e] = 1.0f;
-      post[e] = 1.0f;
+    for (int o = 0; o < 8; ++o) x[o] = *reinterpret_cast<const f32x4*>(&ls.qtot[o][4 * cq]);
+    f32x4 tot = x[0], pre = {1.0f, 1.0f, 1.0f, 1.0f}, post = pre, own_lo = x[0], own_hi = x[1];
+#pragma unroll
+    for (int o = 1; o < 8; ++o) {
+      if (o < 7 && o == 2 * wave) {
+        pre = tot;
+        own_lo = x[o];
+        own_hi = x[(o + 1) & 7];
+      }
+      tot *= x[o];
     }
 #pragma unroll
-    for (int o = 0; o < 8; ++o) {
-      const float4 x = *reinterpret_cast<const float4*>(&ls.qtot[o][4 * cq]);
-      const float xs[4] = {x.x, x.y, x.z, x.w};
+    for (int o = 7; o > 1; --o)
+      if (o > 2 * wave + 1) post *= x[o];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (o < oc) pre[e] *= xs[e];
-        if (o > oc) post[e] *= xs[e];
-        tot[e] *= xs[e];
-      }
+    for (int e = 0; e < 4; ++e) {
+      pre[e] = hf ? pre[e] * own_lo[e] : pre[e];
+      post[e] = hf ? post[e] : post[e] * own_hi[e];
     }
     // gamma_t = pre * g, gamma_C / gamma_t = sfx * post (a product of the later decays, no division),
     // and k / gamma_t = (k gamma_C / gamma_t) / gamma_C: one reciprocal per channel
@@ -312,6 +328,8 @@ __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, co
     }
     {
       __bf16 kb[4][8];
+      ld.open(alpha, k, q, beta, nxt, H, tid);
+      ld.write_strength(raw);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int t = 8 * oc + i;
@@ -330,18 +348,19 @@ __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, co
         *reinterpret_cast<bf16x4*>(&ls.qt[t * QS + 4 * cq]) = vq;
         *reinterpret_cast<bf16x4*>(&ls.kt[t * QS + 4 * cq]) = vk;
         *reinterpret_cast<bf16x4*>(&ls.kr[t * RS + 4 * cq]) = vr;
+        ld.row(raw, i, tok_stride);
+        keep_order();
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        __bf16* kp = &ls.kbt[buf][(4 * cq + e) * CS + 8 * oc];
-        *reinterpret_cast<bf16x4*>(kp) = bf16x4{kb[e][0], kb[e][1], kb[e][2], kb[e][3]};
-        *reinterpret_cast<bf16x4*>(kp + 4) = bf16x4{kb[e][4], kb[e][5], kb[e][6], kb[e][7]};
+        *reinterpret_cast<bf16x4*>(&ls.kbt[buf][kbt_at(4 * cq + e, 8 * oc)]) = bf16x4{kb[e][0], kb[e][1], kb[e][2], kb[e][3]};
+        *reinterpret_cast<bf16x4*>(&ls.kbt[buf][kbt_at(4 * cq + e, 8 * oc + 4)]) = bf16x4{kb[e][4], kb[e][5], kb[e][6], kb[e][7]};
       }
       if (oc == 0) *reinterpret_cast<float4*>(&ls.gc[buf][4 * cq]) = make_float4(tot[0], tot[1], tot[2], tot[3]);
     }
     // compact list of the slow channels, in channel order (lanes 0-31 of every wave see all channels)
     int nslow = 0;
-    {
+    if (__ballot(slow[0] || slow[1] || slow[2] || slow[3])) {
       const uint64_t lo32 = (lane < 32) ? ((lane == 0) ? 0ull : (~0ull >> (64 - lane))) : 0ull;
       int below = 0;
 #pragma unroll
@@ -350,7 +369,6 @@ __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, co
         below += __popcll(b & lo32);
         nslow += __popcll(b);
       }
-      if (tid == 0) ls.nslow = nslow;
       if (wave == 0 && lane < 32) {
         int idx = below;
 #pragma unroll
@@ -358,41 +376,33 @@ __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, co
           if (slow[e]) ls.slow_list[idx++] = 4 * cq + e;
       }
     }
+    if (tid == 0) ls.nslow = nslow;
     lds_barrier();   // 2
 
     // ---- A and P (waves 0-2: tiles (0,0), (1,0), (1,1)) ------------------------------------------
-    if (nxt.valid) load_raw_alpha(raw, alpha, nxt, tok_stride, tid);
     const int tb1 = wave == 0 ? 0 : 1, sb1 = wave == 2 ? 1 : 0;
+    // transposed tiles (rows s, lane = row t of A and P), so that a lane writes four consecutive s at once
     f32x16 accA = {}, accP = {};
     if (wave < 3) {
-      // the operands of step kc + 1 are read while step kc's two products run
+      // the operands of step kc + 3 are read while step kc's two products run
       const __bf16* kp = &ls.kt[(32 * tb1 + col) * QS + 8 * hf];
       const __bf16* qp = &ls.qt[(32 * tb1 + col) * QS + 8 * hf];
       const __bf16* rp = &ls.kr[(32 * sb1 + col) * RS + 8 * hf];
       auto ld4 = [](const __bf16* p) { return cat(*reinterpret_cast<const bf16x4*>(p), *reinterpret_cast<const bf16x4*>(p + 4)); };
-      bf16x8 ak = ld4(kp), aq = ld4(qp), b = *reinterpret_cast<const bf16x8*>(rp);
+      bf16x8 ak[3], aq[3], b[3];
 #pragma unroll
-      for (int kc = 0; kc < kD / 16; ++kc) {
-        bf16x8 nk = ak, nq = aq, nb = b;
-        if (kc + 1 < kD / 16) {
-          nk = ld4(kp + 16 * (kc + 1));
-          nq = ld4(qp + 16 * (kc + 1));
-          nb = *reinterpret_cast<const bf16x8*>(rp + 16 * (kc + 1));
+      for (int kc = 0; kc < kD / 16 + 3; ++kc) {
+        if (kc >= 3) {
+          accA = mfma(b[kc % 3], ak[kc % 3], accA);
+          accP = mfma(b[kc % 3], aq[kc % 3], accP);
         }
-        accA = mfma(ak, b, accA);
-        accP = mfma(aq, b, accP);
-        ak = nk;
-        aq = nq;
-        b = nb;
+        if (kc < kD / 16) {
+          ak[kc % 3] = ld4(kp + 16 * kc);
+          aq[kc % 3] = ld4(qp + 16 * kc);
+          b[kc % 3] = *reinterpret_cast<const bf16x8*>(rp + 16 * kc);
+        }
+        keep_order();
       }
-      // keep the scheduler from sinking the reads back next to their products
-      __builtin_amdgcn_sched_group_barrier(0x100, 5, 0);
-#pragma unroll
-      for (int i = 0; i < kD / 16 - 1; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 5, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
     }
     // slow channels: exact pairwise terms in log2 space, 16 channels per batch, re-read from memory
     for (int base = 0; base < nslow; base += kSlowBatch) {
@@ -429,90 +439,87 @@ __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, co
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int t = 4 * tg + u;
-          ls.kbt[buf][ch * CS + t] = static_cast<__bf16>(ls.slow.k[cl][t] * exp2f(gC - ls.slow.g[cl][t]));
+          ls.kbt[buf][kbt_at(ch, t)] = static_cast<__bf16>(ls.slow.k[cl][t] * exp2f(gC - ls.slow.g[cl][t]));
         }
       }
       if (wave < 3) {
         const int nb = min(kSlowBatch, nslow - base);
-        const int s = 32 * sb1 + col;
+        const int t = 32 * tb1 + col;
         for (int c = 0; c < nb; ++c) {
-          const float gs = ls.slow.g[c][s], ks = ls.slow.k[c][s];
+          const float gt = ls.slow.g[c][t], kt = ls.slow.k[c][t], qt = ls.slow.q[c][t];
 #pragma unroll
           for (int reg = 0; reg < 16; ++reg) {
-            const int t = 32 * tb1 + 8 * (reg >> 2) + 4 * hf + (reg & 3);
-            const float e = exp2f(fminf(ls.slow.g[c][t] - gs, 0.0f)) * ks;
-            accA[reg] += ls.slow.k[c][t] * e;
-            accP[reg] += ls.slow.q[c][t] * e;
+            const int s = 32 * sb1 + 8 * (reg >> 2) + 4 * hf + (reg & 3);
+            const float e = exp2f(fminf(gt - ls.slow.g[c][s], 0.0f)) * ls.slow.k[c][s];
+            accA[reg] += kt * e;
+            accP[reg] += qt * e;
           }
         }
       }
     }
     if (nslow > 0) lds_barrier();   // the batch scratch shares storage with A
     if (wave < 3) {
-      const int s = 32 * sb1 + col;
-      float4 btv[4];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) btv[b] = *reinterpret_cast<const float4*>(&ls.beta[buf][32 * tb1 + 8 * b + 4 * hf]);
+      int t = 32 * tb1 + col;
+      const float bt = ls.beta[buf][t];
+      asm volatile("" : "+v"(t));   // the comparisons stay here: hoisted, their masks spill
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
-        const int t0 = 32 * tb1 + 8 * b + 4 * hf;
-        const float bs[4] = {btv[b].x, btv[b].y, btv[b].z, btv[b].w};
+        const int s0 = 32 * sb1 + 8 * b + 4 * hf;
+        f32x4 av;
+        bf16x4 pv;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int t = t0 + r;
-          ls.a[t * AS + s] = s < t ? accA[4 * b + r] * bs[r] : 0.0f;
-          ls.pm[t * CS + s] = static_cast<__bf16>(s <= t ? accP[4 * b + r] : 0.0f);
+          av[r] = s0 + r < t ? accA[4 * b + r] * bt : 0.0f;
+          pv[r] = static_cast<__bf16>(s0 + r <= t ? accP[4 * b + r] : 0.0f);
         }
+        *reinterpret_cast<f32x4*>(&ls.a[t * AS + s0]) = av;
+        *reinterpret_cast<bf16x4*>(&ls.pm[t * CS + s0]) = pv;
       }
     }
     lds_barrier();   // 3
 
     // ---- T = (I + A)^-1 -----------------------------------------------------------------------
-    if (nxt.valid) load_raw_kqb(raw, k, q, beta, nxt, tok_stride, H, tid);
     // Each wave owns one 16 x 16 diagonal block and needs no barrier for it: the two 8 x 8 halves by
-    // forward substitution (16 lanes, one column each, its coefficients read before the first step),
+    // substitution (every lane one column and one row of a half's inverse, from coefficients read once),
     // then T = D - D (L D) with D the halves' inverses and L the block's lower-left 8 x 8, on fp32
     // MFMAs.  16 -> 32 is the same product (fp32 MFMAs, one wave per pair), 32 -> 64 runs on bf16 MFMAs
     // split over the four waves.  A 16x16 accumulator (lane group g holds rows 4g + r) is the B operand
     // of the next product when its contraction slots are taken in that order.  The phase is a latency
     // chain, so the steps are few and wide: substitution over all 16 rows and the 16 -> 32 sums on the
-    // VALU took 7,400 of a block's 23,600 cycles (4 x 64-head wave of 4,096 tokens: 588 us, now 510).
+    // VALU took 7,400 of a block's 23,600 cycles (4 x 64-head wave of 4,096 tokens: 588 us, then 510).
     {
       const int a0 = 16 * wave, n16 = lane & 15, g16 = lane >> 4;
       const float* ab = &ls.a[a0 * AS + a0];
       float* tb = &ls.tf[a0 * AS + a0];
-      if (lane < 16) {
-        const int s8 = lane & 8, jc = lane & 7;
-        float c[8][8], xs[8];
+      const int s8 = lane & 8, jc = lane & 7;
+      const f32x4 la = *reinterpret_cast<const f32x4*>(&ab[n16 * AS + 4 * g16]);
+      f32x4 c[8][2];
 #pragma unroll
-        for (int t = 1; t < 8; ++t)
+      for (int t = 1; t < 8; ++t)
 #pragma unroll
-          for (int h = 0; h < 2; ++h)
-            if (4 * h < t) {
-              const float4 x = *reinterpret_cast<const float4*>(&ab[(s8 + t) * AS + s8 + 4 * h]);
-              c[t][4 * h] = x.x;
-              c[t][4 * h + 1] = x.y;
-              c[t][4 * h + 2] = x.z;
-              c[t][4 * h + 3] = x.w;
-            }
+        for (int h = 0; h < 2; ++h)
+          if (4 * h < t) c[t][h] = *reinterpret_cast<const f32x4*>(&ab[(s8 + t) * AS + s8 + 4 * h]);
+      float xc[8], xr[8];          // column jc and row jc of the half's inverse
 #pragma unroll
-        for (int t = 0; t < 8; ++t) xs[t] = (t == jc) ? 1.0f : 0.0f;
+      for (int t = 0; t < 8; ++t) xc[t] = xr[t] = (t == jc) ? 1.0f : 0.0f;
 #pragma unroll
-        for (int u = 0; u < 7; ++u)
+      for (int u = 0; u < 7; ++u)
 #pragma unroll
-          for (int t = u + 1; t < 8; ++t) xs[t] -= c[t][u] * xs[u];
+        for (int t = u + 1; t < 8; ++t) {
+          xc[t] -= c[t][u >> 2][u & 3] * xc[u];
+          // row: T[jc][u'] -= T[jc][t'] A[t'][u'] with t' = 7 - u, u' = 7 - t descending
+          xr[7 - t] -= c[7 - u][(7 - t) >> 2][(7 - t) & 3] * xr[7 - u];
+        }
+      // lane group g holds rows (columns) 4g + r: non-zero only inside the lane's own half
+      const int part = g16 - (s8 >> 2);
+      float da[4], db[4];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) tb[(s8 + t) * AS + s8 + jc] = xs[t];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) tb[(s8 + t) * AS + (8 - s8) + jc] = 0.0f;   // the other half's columns
+      for (int r = 0; r < 4; ++r) {
+        db[r] = part == 0 ? xc[r] : part == 1 ? xc[4 + r] : 0.0f;
+        da[r] = part == 0 ? xr[r] : part == 1 ? xr[4 + r] : 0.0f;
       }
       f32x4 lx = f32x4{}, ly = f32x4{};
-      const f32x4 la = *reinterpret_cast<const f32x4*>(&ab[n16 * AS + 4 * g16]);
-      const f32x4 da = *reinterpret_cast<const f32x4*>(&tb[n16 * AS + 4 * g16]);
-      float db[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) db[r] = tb[(4 * g16 + r) * AS + n16];
-      const bool low = n16 >= 8 && g16 < 2;
+      const bool low = s8 && g16 < 2;
 #pragma unroll
       for (int r = 0; r < 4; ++r) lx = mfma_f32(low ? la[r] : 0.0f, db[r], lx);
 #pragma unroll
@@ -583,134 +590,98 @@ __device__ __forceinline__ void run_blocks(const KdaDevPlan& p, KdaLds& ls, cons
   const int H = p.num_heads;
   const int64_t tok_stride = int64_t(H) * kD;
   const int j0 = 32 * wave;                             // this wave's state columns
-  const int mrow = lane >> 2, mpart = 8 * (lane & 3);   // 16-byte moves of V and O: rows mrow + 16 i
-  __bf16* vo = ls.vo[wave];
+  const int mrow = lane >> 2, mpart = 8 * (lane & 3);   // 16-byte moves of V: rows mrow + 16 i
+  const int64_t v_lane = mrow * tok_stride + j0 + mpart, o_lane = col * tok_stride + j0 + 8 * hf;
+  __bf16* vt = ls.vt[wave];
   Cursor cur, nxt;
   nxt.open(p);
   // state tile ib, register 4b + r: row i = 32 ib + 8 b + 4 hf + r, column j0 + col
   f32x16 S[4], accE[2], accO[2];
   bf16x8 uB[2][2];
   for (int buf = 1;; buf ^= 1) {   // block n has buffer buf, block n + 1 the other; the first pass has no block n
-    uint4 vraw[4];
+    u32x4 vraw[4] = {};
     if (nxt.valid) {
+      lds_barrier();   // 1
+      const __bf16* src = v + nxt.tok0() * tok_stride + int64_t(nxt.head) * kD + v_lane;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        vraw[i] = *reinterpret_cast<const uint4*>(v + (nxt.tok0() + min(mrow + 16 * i, nxt.rows() - 1)) * tok_stride +
-                                                  int64_t(nxt.head) * kD + j0 + mpart);
+        if (mrow + 16 * i < nxt.rows()) vraw[i] = *reinterpret_cast<const u32x4*>(src + 16 * i * tok_stride);
     }
     if (cur.valid) {
-      // R = beta (V - E), in place in accE.  V[t0 + r][j] for r = 0..3 comes from the transposing
-      // read: lane 4m + g of each 16-lane group addresses row t0 + m at column 4g of its group.
+      // U = T R with R = beta (V - E) (T lower-triangular: block row tb uses block columns sb <= tb).  T's
+      // operands in the order (tb, sb, kk) = (0,0,0) (0,0,1) (1,0,0) (1,0,1) (1,1,0) (1,1,1), V and beta are
+      // read before any is used.  V[t0 + r][j] for r = 0..3 comes from the transposing read: lane 4m + g
+      // of each 16-lane group addresses row t0 + m at column 4g of its group.
       const int grp = lane >> 4, li = lane & 15;
       const int jg = 16 * (grp & 1) + 4 * (li & 3);
+      bf16x4 vv[2][4];
+      f32x4 bt[2][4];
+      bf16x8 ta[6];
 #pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
-        // the four V fragments and betas of a block row are read before any is used
-        bf16x4 vv[4];
-        float4 bt[4];
+      for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
           const int t0 = 32 * tb + 8 * b + 4 * hf;
-          vv[b] = lds_read_tr(&vo[(t0 + (li >> 2)) * VW + jg]);
-          bt[b] = *reinterpret_cast<const float4*>(&ls.beta[buf][t0]);
+          vv[tb][b] = lds_read_tr(&vt[(t0 + (li >> 2)) * VW + jg]);
+          bt[tb][b] = *reinterpret_cast<const f32x4*>(&ls.beta[buf][t0]);
         }
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const float bs[4] = {bt[b].x, bt[b].y, bt[b].z, bt[b].w};
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            accE[tb][4 * b + r] = bs[r] * (static_cast<float>(vv[b][r]) - accE[tb][4 * b + r]);
-        }
-      }
+      for (int n = 0; n < 6; ++n) ta[n] = lds_a_perm(&ls.tm[(32 * (n < 2 ? 0 : 1) + col) * CS], 32 * (n < 4 ? 0 : 1) + 16 * (n & 1) + 4 * hf);
+      keep_order();
+      f32x16 accU[2] = {};
       bf16x8 rB[2][2];
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            accE[tb][4 * b + r] = bt[tb][b][r] * (static_cast<float>(vv[tb][b][r]) - accE[tb][4 * b + r]);
         rB[tb][0] = acc_to_b(accE[tb], 0);
         rB[tb][1] = acc_to_b(accE[tb], 1);
       }
-      // U = T R (T lower-triangular: block row tb uses block columns sb <= tb).  The six products
-      // run in the order (tb, sb, kk) = (0,0,0) (0,0,1) (1,0,0) (1,0,1) (1,1,0) (1,1,1); each A
-      // operand is read while the previous product runs.  O += P U below uses the same order.
-      f32x16 accU[2] = {};
-      {
-        bf16x8 a = lds_a_perm(&ls.tm[col * CS], 4 * hf);
 #pragma unroll
-        for (int n = 0; n < 6; ++n) {
-          const int tb = n < 2 ? 0 : 1, sb = n < 4 ? 0 : 1, kk = n & 1;
-          bf16x8 na = a;
-          if (n + 1 < 6) {
-            const int m = n + 1;
-            na = lds_a_perm(&ls.tm[(32 * (m < 2 ? 0 : 1) + col) * CS], 32 * (m < 4 ? 0 : 1) + 16 * (m & 1) + 4 * hf);
-          }
-          accU[tb] = mfma(a, rB[sb][kk], accU[tb]);
-          a = na;
-        }
-      }
+      for (int n = 0; n < 6; ++n) accU[n < 2 ? 0 : 1] = mfma(ta[n], rB[n < 4 ? 0 : 1][n & 1], accU[n < 2 ? 0 : 1]);
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb) {
         uB[tb][0] = acc_to_b(accU[tb], 0);
         uB[tb][1] = acc_to_b(accU[tb], 1);
       }
-    }
-    if (nxt.valid) lds_barrier();   // 1
-    if (cur.valid) {
-      // O += P U; the outputs go to LDS over V, rows 4 apart on distinct banks (out_row)
-      {
-        bf16x8 a = lds_a_perm(&ls.pm[col * CS], 4 * hf);
+      // S = Diag(gamma_C) S + Kbar^T U, 16 products in the order (ib, sb, kk), and O += P U; operands are
+      // read four products ahead, the decays of block row ib + 1 while block row ib is updated
+      bf16x8 pa[6], a[4];
+      f32x4 gm[2][4];
 #pragma unroll
-        for (int n = 0; n < 6; ++n) {
-          const int tb = n < 2 ? 0 : 1, sb = n < 4 ? 0 : 1, kk = n & 1;
-          bf16x8 na = a;
-          if (n + 1 < 6) {
-            const int m = n + 1;
-            na = lds_a_perm(&ls.pm[(32 * (m < 2 ? 0 : 1) + col) * CS], 32 * (m < 4 ? 0 : 1) + 16 * (m & 1) + 4 * hf);
+      for (int b = 0; b < 4; ++b) gm[0][b] = *reinterpret_cast<const f32x4*>(&ls.gc[buf][8 * b + 4 * hf]);
+#pragma unroll
+      for (int n = 0; n < 6; ++n) pa[n] = lds_a_perm(&ls.pm[(32 * (n < 2 ? 0 : 1) + col) * CS], 32 * (n < 4 ? 0 : 1) + 16 * (n & 1) + 4 * hf);
+      auto kbt_op = [&](int m) {
+        const int c = 32 * (m >> 2) + col, t = 32 * ((m >> 1) & 1) + 16 * (m & 1) + 4 * hf;
+        return cat(*reinterpret_cast<const bf16x4*>(&ls.kbt[buf][kbt_at(c, t)]), *reinterpret_cast<const bf16x4*>(&ls.kbt[buf][kbt_at(c, t + 8)]));
+      };
+#pragma unroll
+      for (int n = 0; n < 4; ++n) a[n] = kbt_op(n);
+      keep_order();
+#pragma unroll
+      for (int n = 0; n < 6; ++n) accO[n < 2 ? 0 : 1] = mfma(uB[n < 4 ? 0 : 1][n & 1], pa[n], accO[n < 2 ? 0 : 1]);
+#pragma unroll
+      for (int n = 0; n < 16; ++n) {
+        const int ib = n >> 2, sb = (n >> 1) & 1, kk = n & 1;
+        if ((n & 3) == 0) {
+          if (ib + 1 < 4) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+              gm[(ib + 1) & 1][b] = *reinterpret_cast<const f32x4*>(&ls.gc[buf][32 * (ib + 1) + 8 * b + 4 * hf]);
           }
-          accO[tb] = mfma(a, uB[sb][kk], accO[tb]);
-          a = na;
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) S[ib][4 * b + r] *= gm[ib & 1][b][r];
         }
-      }
-#pragma unroll
-      for (int tb = 0; tb < 2; ++tb) {
-#pragma unroll
-        for (int reg = 0; reg < 16; ++reg) {
-          const int t = 32 * tb + 8 * (reg >> 2) + 4 * hf + (reg & 3);
-          vo[out_row(t) * VW + col] = static_cast<__bf16>(accO[tb][reg]);
-        }
-      }
-      // S = Diag(gamma_C) S + Kbar^T U: 16 products in the order (ib, sb, kk), each A operand read
-      // while the previous product runs
-      {
-        bf16x8 a = lds_a_perm(&ls.kbt[buf][col * CS], 4 * hf);
-        // the decays of block row ib + 1 are read while block row ib is updated
-        float4 gcur[4], gnxt[4];
-#pragma unroll
-        for (int b = 0; b < 4; ++b) gcur[b] = *reinterpret_cast<const float4*>(&ls.gc[buf][8 * b + 4 * hf]);
-#pragma unroll
-        for (int n = 0; n < 16; ++n) {
-          const int ib = n >> 2, sb = (n >> 1) & 1, kk = n & 1;
-          if ((n & 3) == 0) {
-            if (ib + 1 < 4) {
-#pragma unroll
-              for (int b = 0; b < 4; ++b)
-                gnxt[b] = *reinterpret_cast<const float4*>(&ls.gc[buf][32 * (ib + 1) + 8 * b + 4 * hf]);
-            }
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-              S[ib][4 * b + 0] *= gcur[b].x;
-              S[ib][4 * b + 1] *= gcur[b].y;
-              S[ib][4 * b + 2] *= gcur[b].z;
-              S[ib][4 * b + 3] *= gcur[b].w;
-              gcur[b] = gnxt[b];
-            }
-          }
-          bf16x8 na = a;
-          if (n + 1 < 16) {
-            const int m = n + 1;
-            na = lds_a_perm(&ls.kbt[buf][(32 * (m >> 2) + col) * CS], 32 * ((m >> 1) & 1) + 16 * (m & 1) + 4 * hf);
-          }
-          S[ib] = mfma(a, uB[sb][kk], S[ib]);
-          a = na;
-        }
+        const bf16x8 cur_a = a[n & 3];
+        if (n + 4 < 16) a[n & 3] = kbt_op(n + 4);
+        keep_order();
+        S[ib] = mfma(cur_a, uB[sb][kk], S[ib]);
       }
     }
     if (nxt.valid) {
@@ -720,21 +691,38 @@ __device__ __forceinline__ void run_blocks(const KdaDevPlan& p, KdaLds& ls, cons
         for (int i = 0; i < 3; ++i) lds_barrier();
       if (slow > 0) lds_barrier();
     }
-    if (cur.valid) {
-      const int L = cur.rows();
-      __bf16* dst = out + cur.tok0() * tok_stride + int64_t(cur.head) * kD + j0 + mpart;
+    // O^T tile tb: lane = row 32 tb + col, register 4 b + r = column 8 b + 4 hf + r of the wave's 32.  The
+    // half-waves trade registers so that each lane stores 8 consecutive columns.
+    u32x4 ow[2][2];
+    const int out_rows = cur.valid ? cur.rows() - col : 0;
+    __bf16* out_at = out + cur.tok0() * tok_stride + int64_t(cur.head) * kD + o_lane;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int t = mrow + 16 * i;
-        if (t < L) *reinterpret_cast<uint4*>(dst + t * tok_stride) = *reinterpret_cast<const uint4*>(&vo[out_row(t) * VW + mpart]);
+    for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const u32x4 x = __builtin_bit_cast(u32x4, acc_to_b(accO[tb], h));   // columns 16 h + 4 hf .. and 8 further
+        const auto lo = __builtin_amdgcn_permlane32_swap(x[0], x[2], false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(x[1], x[3], false, false);
+        ow[tb][h] = u32x4{lo[0], hi[0], lo[1], hi[1]};
       }
-      if (cur.last()) {            // snapshot at the chunk boundary
-        float* st = state_pool + (int64_t(cur.state_out) * H + cur.head) * kD * kD + j0 + col;
+    auto store_out = [&](int tb, int h) {
+      if (32 * tb < out_rows) *reinterpret_cast<u32x4*>(out_at + 32 * tb * tok_stride + 16 * h) = ow[tb][h];
+    };
+    if (!nxt.valid) {
 #pragma unroll
-        for (int ib = 0; ib < 4; ++ib)
+      for (int i = 0; i < 4; ++i) store_out(i >> 1, i & 1);
+    } else {
+      // (before any store of this period: the wait for these loads would wait for the stores too)
 #pragma unroll
-          for (int reg = 0; reg < 16; ++reg) st[(32 * ib + 8 * (reg >> 2) + 4 * hf + (reg & 3)) * kD] = S[ib][reg];
-      }
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<u32x4*>(&vt[(mrow + 16 * i) * VW + mpart]) = vraw[i];
+    }
+    if (cur.valid && cur.last()) {            // snapshot at the chunk boundary
+      float* st = state_pool + (int64_t(cur.state_out) * H + cur.head) * kD * kD + j0 + col;
+#pragma unroll
+      for (int ib = 0; ib < 4; ++ib)
+#pragma unroll
+        for (int reg = 0; reg < 16; ++reg) st[(32 * ib + 8 * (reg >> 2) + 4 * hf + (reg & 3)) * kD] = S[ib][reg];
     }
     if (!nxt.valid) break;
     if (nxt.blk == 0) {
@@ -748,32 +736,27 @@ __device__ __forceinline__ void run_blocks(const KdaDevPlan& p, KdaLds& ls, cons
           for (int reg = 0; reg < 16; ++reg) S[ib][reg] = st[(32 * ib + 8 * (reg >> 2) + 4 * hf + (reg & 3)) * kD];
       }
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<uint4*>(&vo[(mrow + 16 * i) * VW + mpart]) = mrow + 16 * i < nxt.rows() ? vraw[i] : make_uint4(0, 0, 0, 0);
-    // E = K~ S0 and O = Q~ S0, one step of the contraction ahead of the products; barriers 3 to 6 fall
-    // between its steps about where the builders reach them
+    // E = K~ S0 and O^T = (Q~ S0)^T, operands read three steps ahead; block n's outputs leave
+    // between the steps, and barriers 3 to 6 fall about where the builders reach them
     accE[0] = accE[1] = accO[0] = accO[1] = f32x16{};
     {
-      bf16x8 sB[2];
-      bf16x8 ak = lds_a_perm(&ls.kt[col * QS], 4 * hf);
-      bf16x8 aq = lds_a_perm(&ls.qt[col * QS], 4 * hf);
+      bf16x8 sB[2], ak[3], aq[3];
 #pragma unroll
-      for (int n = 0; n < 16; ++n) {
-        const int ib = n >> 2, kk = (n >> 1) & 1, tb = n & 1;
-        if (tb == 0) sB[kk] = acc_to_b(S[ib], kk);
-        bf16x8 nk = ak, nq = aq;
-        if (n + 1 < 16) {
-          const int m = n + 1;
-          const int cb = 32 * (m >> 2) + 16 * ((m >> 1) & 1) + 4 * hf;
-          nk = lds_a_perm(&ls.kt[(32 * (m & 1) + col) * QS], cb);
-          nq = lds_a_perm(&ls.qt[(32 * (m & 1) + col) * QS], cb);
+      for (int n = 0; n < 16 + 3; ++n) {
+        if (n >= 3) {
+          const int m = n - 3, ib = m >> 2, kk = (m >> 1) & 1, tb = m & 1;
+          if (tb == 0) sB[kk] = acc_to_b(S[ib], kk);
+          accE[tb] = mfma(ak[n % 3], sB[kk], accE[tb]);
+          accO[tb] = mfma(sB[kk], aq[n % 3], accO[tb]);
+          if (m == 2 || m == 5 || m == 8 || m == 11) store_out((m - 2) / 6, ((m - 2) / 3) & 1);
+          if (m == 5 || m == 13 || m == 14 || m == 15) lds_barrier();   // 3, 4, 5, 6
         }
-        accE[tb] = mfma(ak, sB[kk], accE[tb]);
-        accO[tb] = mfma(aq, sB[kk], accO[tb]);
-        ak = nk;
-        aq = nq;
-        if (n == 3 || n == 8 || n == 11 || n == 15) lds_barrier();   // 3, 4, 5, 6
+        if (n < 16) {
+          const int cb = 32 * (n >> 2) + 16 * ((n >> 1) & 1) + 4 * hf;
+          ak[n % 3] = lds_a_perm(&ls.kt[(32 * (n & 1) + col) * QS], cb);
+          aq[n % 3] = lds_a_perm(&ls.qt[(32 * (n & 1) + col) * QS], cb);
+        }
+        keep_order();
       }
     }
     cur = nxt;
