@@ -52,20 +52,19 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 // ---------------------------------------------------------------------------------------------
 // Append: token t of request r -> page bt[r][(p_r + i) / B], slot (p_r + i) % B, all KV heads.
-// One workgroup moves kAppendTokens consecutive packed tokens; for each token its threads move the
+// One workgroup moves TOK consecutive packed tokens; for each token its threads move the
 // Hkv * (DK + DV) / 8 16-byte chunks (the workgroup has that many threads rounded up to a whole
-// wave, at most 256).  The token's request and page are uniform across the
-// workgroup, so they are looked up once, with scalar loads through the constant address space
-// (the kernel never writes the metadata).
+// wave, at most 256).  The token's request and page are uniform across the workgroup, so they are
+// looked up once, with scalar loads through the constant address space (the kernel never writes the
+// metadata).  A small wave is a chain of dependent loads (request, page, then the store), so it takes
+// one token per workgroup (launch_append), and the rows to be moved are loaded before the lookup.
 // ---------------------------------------------------------------------------------------------
-constexpr int kAppendTokens = 8;
-
 template <typename T>
 __device__ __forceinline__ T const_load(const T* ptr) {
   return *((const __attribute__((address_space(4))) T*)(ptr));
 }
 
-template <int DK, int DV>
+template <int DK, int DV, int TOK>
 __global__ __launch_bounds__(256) void append_kernel(DevPlan p, const uint4* __restrict__ k_new,
                                                      const uint4* __restrict__ v_new, uint4* __restrict__ k_pool,
                                                      uint4* __restrict__ v_pool) {
@@ -75,16 +74,29 @@ __global__ __launch_bounds__(256) void append_kernel(DevPlan p, const uint4* __r
   const int per_tok = Hkv * UC;
   const int B = p.page_size;
   const int64_t T = p.total_tokens;
-  const int64_t t0 = int64_t(blockIdx.x) * kAppendTokens;
-  // request holding token t0: the last r with cu_r <= t0 (requests with no chunk share cu with the next)
+  const int64_t t0 = int64_t(blockIdx.x) * TOK;
+  auto load = [&](int64_t t, int u) {
+    const int h = u / UC, c = u - h * UC;
+    return c < KC ? k_new[(t * Hkv + h) * KC + c] : v_new[(t * Hkv + h) * VC + c - KC];
+  };
+  uint4 first[TOK];
+#pragma unroll
+  for (int i = 0; i < TOK; ++i)
+    if (t0 + i < T && int(threadIdx.x) < per_tok) first[i] = load(t0 + i, threadIdx.x);
+  // request holding token t0: the last r with cu_r <= t0 (requests with no chunk share cu with the next).
+  // Bisection leaves at most 64 candidates, then every lane looks at one.
   int lo = 0, hi = p.num_requests - 1;
-  while (lo < hi) {
+  while (hi - lo >= 64) {
     const int mid = (lo + hi + 1) >> 1;
     if (const_load(&p.reqs[mid].cu) <= t0) lo = mid; else hi = mid - 1;
   }
   int r = lo;
+  if (hi > lo) {
+    const int mine = lo + int(threadIdx.x & 63);
+    r = lo + __popcll(__ballot(mine <= hi && p.reqs[min(mine, hi)].cu <= t0)) - 1;
+  }
 #pragma unroll
-  for (int i = 0; i < kAppendTokens; ++i) {
+  for (int i = 0; i < TOK; ++i) {
     const int64_t t = t0 + i;
     if (t >= T) break;
     while (r + 1 < p.num_requests && const_load(&p.reqs[r + 1].cu) <= t) ++r;
@@ -95,12 +107,11 @@ __global__ __launch_bounds__(256) void append_kernel(DevPlan p, const uint4* __r
     for (int u = threadIdx.x; u < per_tok; u += blockDim.x) {
       const int h = u / UC;
       const int c = u - h * UC;
-      if (c < KC) {
-        k_pool[((page * Hkv + h) * B + slot) * KC + c] = k_new[(t * Hkv + h) * KC + c];
-      } else {
-        const int cv = c - KC;
-        v_pool[((page * Hkv + h) * B + slot) * VC + cv] = v_new[(t * Hkv + h) * VC + cv];
-      }
+      const uint4 x = u == int(threadIdx.x) ? first[i] : load(t, u);
+      if (c < KC)
+        k_pool[((page * Hkv + h) * B + slot) * KC + c] = x;
+      else
+        v_pool[((page * Hkv + h) * B + slot) * VC + c - KC] = x;
     }
   }
 }
@@ -962,7 +973,9 @@ hipError_t launch_append(const DevPlan& p, const void* k_new, const void* v_new,
                          hipStream_t stream) {
   const int dk = p.head_dim_qk, dv = p.kv_shared ? 0 : p.head_dim_v;
   if (p.total_tokens == 0) return hipSuccess;
-  const int64_t blocks = (p.total_tokens + kAppendTokens - 1) / kAppendTokens;
+  // one token per workgroup up to 2,048 tokens (fewer than eight workgroups per CU), eight beyond
+  const bool few = p.total_tokens <= 2048;
+  const int64_t blocks = few ? p.total_tokens : (p.total_tokens + 7) / 8;
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
   const int per_tok = p.num_kv_heads * ((dk + dv) / 8);
   const int threads = std::min(256, (per_tok + 63) / 64 * 64);
@@ -970,14 +983,19 @@ hipError_t launch_append(const DevPlan& p, const void* k_new, const void* v_new,
   auto vn = static_cast<const uint4*>(v_new);
   auto kp = static_cast<uint4*>(k_pool);
   auto vp = static_cast<uint4*>(v_pool);
-  if (dk == 64 && dv == 64)
-    hipLaunchKernelGGL((append_kernel<64, 64>), dim3(blocks), dim3(threads), 0, stream, p, kn, vn, kp, vp);
-  else if (dk == 128 && dv == 128)
-    hipLaunchKernelGGL((append_kernel<128, 128>), dim3(blocks), dim3(threads), 0, stream, p, kn, vn, kp, vp);
-  else if (dk == 576 && dv == 0)
-    hipLaunchKernelGGL((append_kernel<576, 0>), dim3(blocks), dim3(threads), 0, stream, p, kn, vn, kp, vp);
-  else
+#define WAVEPP_APPEND(DK_, DV_)                                                                                        \
+  if (few) hipLaunchKernelGGL((append_kernel<DK_, DV_, 1>), dim3(blocks), dim3(threads), 0, stream, p, kn, vn, kp, vp); \
+  else hipLaunchKernelGGL((append_kernel<DK_, DV_, 8>), dim3(blocks), dim3(threads), 0, stream, p, kn, vn, kp, vp);
+  if (dk == 64 && dv == 64) {
+    WAVEPP_APPEND(64, 64)
+  } else if (dk == 128 && dv == 128) {
+    WAVEPP_APPEND(128, 128)
+  } else if (dk == 576 && dv == 0) {
+    WAVEPP_APPEND(576, 0)
+  } else {
     return hipErrorInvalidValue;
+  }
+#undef WAVEPP_APPEND
   return hipGetLastError();
 }
 
