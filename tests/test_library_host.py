@@ -421,3 +421,30 @@ def test_noalloc_entry_point_rejects_plans_beyond_its_static_scratch():
     assert b"static scratch" in lib.wavepp_last_error()
     # a plan that fits passes the size check (and then needs a GPU: not called here)
     assert wp.plan_for(spec).workspace_bytes <= 160 << 20
+
+
+@pytest.mark.parametrize("prefix,chunk", [
+    ([16384] * 3, [4, 4, 4]),                     # every piece the same length
+    ([16320, 9000, 1000, 12345], [12, 1, 3, 7]),  # remainders of every size
+    ([4095, 4096, 4097], [40, 40, 40]),           # pieces near the minimum length
+    ([511], [200]),                               # too short to cut
+])
+def test_latent_splits_balance_256_slots(prefix, chunk):
+    """A latent wave below 512 base items: its pieces cover every visible pair once, are whole tiles of at
+    least 512 keys but for an item's last, and handed out longest first to 256 one-at-a-time workgroups the
+    busiest gets at most 1.35 times the even share and 16 tiles, twice the minimum length (uncut, the first
+    wave's busiest would get 256 tiles for an even share of 12)."""
+    import heapq
+    spec = wl.custom_wave(128, 1, 576, 512, 64, prefix, chunk, kv_shared=True, seed=3)
+    it = wp.plan_for(spec).items()
+    coverage_check(spec, it, 64)
+    real = it[it[:, 3] > 0]
+    assert len(real) <= 512
+    tiles = -(-(real[:, 5] - real[:, 4]) // 64)
+    key = [tuple(r[[0, 2]]) for r in real]
+    last = {k: max(int(r[7]) for r, kk in zip(real, key) if kk == k) for k in set(key)}
+    assert all(t >= 8 for t, r, k in zip(tiles, real, key) if int(r[7]) < last[k])
+    busy = [0] * 256
+    for t in sorted(map(int, tiles), reverse=True):
+        heapq.heapreplace(busy, busy[0] + t)
+    assert max(busy) <= 1.35 * tiles.sum() / 256 + 16
