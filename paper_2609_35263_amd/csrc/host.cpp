@@ -132,65 +132,138 @@ double item_cost(const WorkItem& it, int G) {
   return double(it.rows) * std::max(keys, 1.0);
 }
 
+// `slots` workgroups that run one item after another, as a min-heap of the times at which they are free.
+class SlotClock {
+ public:
+  explicit SlotClock(int slots) : busy_(size_t(std::max(1, slots)), 0.0) {}
+  // the next item of `time` goes to the slot that is free first
+  void add(double time) {
+    const double t = busy_[0] + time;
+    longest_ = std::max(longest_, t);
+    const size_t n = busy_.size();
+    size_t i = 0;
+    for (size_t c = 1; c < n; c = 2 * i + 1) {
+      if (c + 1 < n && busy_[c + 1] < busy_[c]) ++c;
+      if (busy_[c] >= t) break;
+      busy_[i] = busy_[c];
+      i = c;
+    }
+    busy_[i] = t;
+  }
+  double longest() const { return longest_; }
+
+ private:
+  std::vector<double> busy_;
+  double longest_ = 0.0;
+};
+
 // Order items heaviest first and spread them over the L2 domains: consecutive workgroup ids go
 // round-robin to the kNumXcd domains, so item index k*kNumXcd + x runs on domain x.  Items of one
-// (request, KV head) read the same K/V pages; keeping them on one domain lets its L2 serve the
-// re-reads.  With few such streams, balance wins and items are placed individually.
+// (request, KV head), a stream, read the same K/V pages; keeping them on one domain lets its L2 serve the
+// re-reads.  With few streams, balance wins and items are placed individually; the same holds where
+// whole streams leave some workgroup slots busy much longer than others.
 // WAVEPP_STREAM_MAJOR=0 keeps each domain's items in plain heaviest-first order.
-std::vector<WorkItem> order_items(std::vector<WorkItem> items, int G, bool xcd_aware, bool stream_major) {
-  std::vector<double> cost(items.size());
-  for (size_t i = 0; i < items.size(); ++i) cost[i] = item_cost(items[i], G);
-  std::vector<size_t> idx(items.size());
-  std::iota(idx.begin(), idx.end(), 0);
-  std::stable_sort(idx.begin(), idx.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
-  if (!xcd_aware || items.size() <= 1) {
+// The items of a stream are consecutive in `items`.  `slots` is the number of workgroups the chip runs at a
+// time, `overhead` an item's prologue and epilogue in tiles of `kv_tile` keys.
+std::vector<WorkItem> order_items(std::vector<WorkItem> items, int G, bool xcd_aware, bool stream_major, int slots,
+                                  int kv_tile, double overhead) {
+  const size_t n = items.size();
+  typedef std::pair<double, uint32_t> Key;   // (size, index): largest first, in index order where equal
+  auto larger = [](const Key& a, const Key& b) { return a.first > b.first || (a.first == b.first && a.second < b.second); };
+  std::vector<Key> by_cost(n);
+  for (size_t i = 0; i < n; ++i) by_cost[i] = Key(item_cost(items[i], G), uint32_t(i));
+  if (!xcd_aware || n <= 1) {
+    std::sort(by_cost.begin(), by_cost.end(), larger);
     std::vector<WorkItem> out;
-    out.reserve(items.size());
-    for (size_t i : idx) out.push_back(items[i]);
+    out.reserve(n);
+    for (const Key& k : by_cost) out.push_back(items[k.second]);
     return out;
   }
-  // streams = (req, kv_head)
-  std::vector<std::pair<int64_t, double>> stream_cost;  // key -> total
-  auto key_of = [](const WorkItem& w) { return (int64_t(w.req) << 32) | uint32_t(w.kv_head); };
-  std::vector<int64_t> keys;
-  for (auto& w : items) keys.push_back(key_of(w));
-  std::vector<int64_t> uniq = keys;
-  std::sort(uniq.begin(), uniq.end());
-  uniq.erase(std::unique(uniq.begin(), uniq.end()), uniq.end());
-  std::vector<double> scost(uniq.size(), 0.0);
-  for (size_t i = 0; i < items.size(); ++i)
-    scost[std::lower_bound(uniq.begin(), uniq.end(), keys[i]) - uniq.begin()] += cost[i];
-  double total = std::accumulate(scost.begin(), scost.end(), 0.0);
-  double biggest = uniq.empty() ? 0.0 : *std::max_element(scost.begin(), scost.end());
-  std::vector<std::vector<size_t>> lists(kNumXcd);
-  std::vector<double> load(kNumXcd, 0.0);
-  bool by_stream = uniq.size() >= size_t(2 * kNumXcd) && biggest <= 0.5 * total / kNumXcd;
-  if (by_stream) {
-    std::vector<size_t> sidx(uniq.size());
-    std::iota(sidx.begin(), sidx.end(), 0);
-    std::stable_sort(sidx.begin(), sidx.end(), [&](size_t a, size_t b) { return scost[a] > scost[b]; });
-    std::vector<int> where(uniq.size(), 0);
-    for (size_t s : sidx) {
-      int x = int(std::min_element(load.begin(), load.end()) - load.begin());
-      where[s] = x;
-      load[x] += scost[s];
+  std::vector<uint32_t> stream(n), first;      // stream of an item, first item of a stream
+  std::vector<Key> by_stream_cost;
+  double total = 0.0, biggest = 0.0;
+  for (size_t i = 0; i < n; ++i) {
+    if (i == 0 || items[i].req != items[i - 1].req || items[i].kv_head != items[i - 1].kv_head) {
+      by_stream_cost.push_back(Key(0.0, uint32_t(first.size())));
+      first.push_back(uint32_t(i));
+    }
+    stream[i] = uint32_t(first.size() - 1);
+    by_stream_cost.back().first += by_cost[i].first;
+    total += by_cost[i].first;
+    biggest = std::max(biggest, by_stream_cost.back().first);
+  }
+  // Time goes by tiles, not rows: an item's workgroup runs its key tiles in the same time however few of its
+  // rows are used.
+  std::vector<double> time(n);
+  double time_sum = 0.0, time_max = 0.0;
+  for (size_t i = 0; i < n; ++i) {
+    time[i] = double(ceil_div(items[i].kv_end - items[i].kv_begin, kv_tile)) + overhead;
+    time_sum += time[i];
+    time_max = std::max(time_max, time[i]);
+  }
+  typedef std::vector<std::vector<uint32_t>> Lists;
+  // individual placement: longest first, each to the least loaded domain
+  auto place_items = [&] {
+    std::vector<Key> by_time(n);
+    for (size_t i = 0; i < n; ++i) by_time[i] = Key(time[i], uint32_t(i));
+    std::sort(by_time.begin(), by_time.end(), larger);
+    Lists out(kNumXcd);
+    double busy[kNumXcd] = {};
+    for (const Key& k : by_time) {
+      const int x = int(std::min_element(busy, busy + kNumXcd) - busy);
+      out[x].push_back(k.second);
+      busy[x] += k.first;
+    }
+    return out;
+  };
+  Lists lists;
+  if (first.size() >= size_t(2 * kNumXcd) && biggest <= 0.5 * total / kNumXcd) {
+    lists.resize(kNumXcd);
+    std::sort(by_cost.begin(), by_cost.end(), larger);
+    std::sort(by_stream_cost.begin(), by_stream_cost.end(), larger);
+    std::vector<int> where(first.size(), 0);
+    double load[kNumXcd] = {};
+    for (const Key& k : by_stream_cost) {
+      const int x = int(std::min_element(load, load + kNumXcd) - load);
+      where[k.second] = x;
+      load[x] += k.first;
     }
     if (stream_major) {
       // inside a domain, stream by stream (heaviest stream first), each stream's items heaviest
       // first: the items running together on the domain's CUs then mostly belong to one stream and
       // read its tiles at about the same time, so the domain's L2 serves the re-reads
-      std::vector<std::vector<size_t>> by(uniq.size());
-      for (size_t i : idx) by[std::lower_bound(uniq.begin(), uniq.end(), keys[i]) - uniq.begin()].push_back(i);
-      for (size_t s : sidx) lists[where[s]].insert(lists[where[s]].end(), by[s].begin(), by[s].end());
+      std::vector<uint32_t> at(first), sorted(n);
+      for (const Key& k : by_cost) sorted[at[stream[k.second]]++] = k.second;
+      for (const Key& k : by_stream_cost) {
+        const size_t end = k.second + 1 < first.size() ? first[k.second + 1] : n;
+        lists[where[k.second]].insert(lists[where[k.second]].end(), sorted.begin() + first[k.second], sorted.begin() + end);
+      }
     } else {
-      for (size_t i : idx) lists[where[std::lower_bound(uniq.begin(), uniq.end(), keys[i]) - uniq.begin()]].push_back(i);
+      for (const Key& k : by_cost) lists[where[stream[k.second]]].push_back(k.second);
+    }
+    // With few items per slot, the last stream of a domain can run on a few of its slots alone.  Both orders
+    // are played through (each domain hands its list to its slots in order); the streams stay together
+    // unless that costs more than 5 %, about what the L2's re-reads are worth (2-4 % on long-prefix waves).
+    // 12 requests of 0.1-6 K cached and 37-1,500 new tokens, 24/4 heads: 125 tiles against 102, 331 us
+    // against 281.
+    if (n <= size_t(16) * slots) {
+      auto makespan = [&](const Lists& ls) {
+        double longest = 0.0;
+        for (const auto& l : ls) {
+          SlotClock clock(slots / kNumXcd);
+          for (uint32_t i : l) clock.add(time[i]);
+          longest = std::max(longest, clock.longest());
+        }
+        return longest;
+      };
+      const double together = makespan(lists);
+      if (std::max(time_max, time_sum / slots) < 0.95 * together) {   // no order is shorter than that
+        Lists single = place_items();
+        if (makespan(single) < 0.95 * together) lists = std::move(single);
+      }
     }
   } else {
-    for (size_t i : idx) {
-      int x = int(std::min_element(load.begin(), load.end()) - load.begin());
-      lists[x].push_back(i);
-      load[x] += cost[i];
-    }
+    lists = place_items();
   }
   size_t longest = 0;
   for (auto& l : lists) longest = std::max(longest, l.size());
@@ -213,26 +286,27 @@ struct SplitPlan {
 
 // Modelled time of a wave of pieces, in tiles: the workgroups are handed out longest first to `slots`
 // that run one at a time, each piece costing its tiles plus `overhead` (queries in, partial out), and
-// every piece of a split item adds its partial rows to the merge.
-double split_cost(const std::vector<int64_t>& ntiles, const SplitPlan& sp, int slots, double overhead, double merge) {
+// every piece of a split item adds its partial rows to the merge.  A plan that cannot beat `best` is not
+// played through.
+double split_cost(const std::vector<int64_t>& ntiles, const SplitPlan& sp, int slots, double overhead, double merge,
+                  double best) {
   std::vector<int64_t> len;
   len.reserve(size_t(sp.pieces));
-  double partials = 0.0;
+  double partials = 0.0, sum = 0.0;
+  int64_t most = 0;
   for (size_t i = 0; i < ntiles.size(); ++i) {
     const int64_t n = ntiles[i], t = sp.tps[i];
     for (int64_t k = 0; k < n; k += t) len.push_back(std::min(t, n - k));
     if (n > t) partials += double(ceil_div(n, t));
+    sum += double(n);
+    most = std::max(most, std::min(n, t));
   }
+  const double bound = std::max(double(most) + overhead, (sum + overhead * double(len.size())) / slots) + merge * partials;
+  if (bound >= best) return bound;
   std::sort(len.begin(), len.end(), std::greater<int64_t>());
-  std::vector<double> busy(size_t(slots), 0.0);   // min-heap
-  double longest = 0.0;
-  for (int64_t n : len) {
-    std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
-    busy.back() += double(n) + overhead;
-    longest = std::max(longest, busy.back());
-    std::push_heap(busy.begin(), busy.end(), std::greater<double>());
-  }
-  return longest + merge * partials;
+  SlotClock clock(slots);
+  for (int64_t n : len) clock.add(double(n) + overhead);
+  return clock.longest() + merge * partials;
 }
 
 }  // namespace
@@ -533,10 +607,10 @@ int wavepp_attn_plan(const wavepp_attn_shape* shape, const wavepp_batch* batch, 
     if (mla && longest >= 2 * min_split_tiles) {
       const int slots = kNumCu;
       const double overhead = 5.0, merge = 0.015;
-      double best = split_cost(ntiles, split, slots, overhead, merge);
+      double best = split_cost(ntiles, split, slots, overhead, merge, INFINITY);
       auto consider = [&](SplitPlan sp) {
         if (sp.pieces > fill_target) return;
-        const double c = split_cost(ntiles, sp, slots, overhead, merge);
+        const double c = split_cost(ntiles, sp, slots, overhead, merge, best);
         if (c < best) {
           best = c;
           split = std::move(sp);
@@ -594,8 +668,10 @@ int wavepp_attn_plan(const wavepp_attn_shape* shape, const wavepp_batch* batch, 
   plan->num_real_items = int32_t(items.size());
   plan->max_splits_used = max_used;
   plan->partial_rows = part_rows;
+  // workgroups per CU: the 4-wave grouped form runs two, or three at head dim 64; the others one
+  const int per_cu = small_rows && !mla ? (s.head_dim_qk == 64 ? 3 : 2) : 1;
   plan->items = order_items(std::move(items), G, env_flag("WAVEPP_XCD_ORDER", true),
-                            env_flag("WAVEPP_STREAM_MAJOR", true));
+                            env_flag("WAVEPP_STREAM_MAJOR", true), per_cu * kNumCu, KT, mla ? 5.0 : 1.0);
   if (plan->items.size() > size_t(INT32_MAX / 2)) {
     delete plan;
     return set_error(WAVEPP_EINVAL, "too many work items");

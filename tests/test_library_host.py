@@ -448,3 +448,28 @@ def test_latent_splits_balance_256_slots(prefix, chunk):
     for t in sorted(map(int, tiles), reverse=True):
         heapq.heapreplace(busy, busy[0] + t)
     assert max(busy) <= 1.35 * tiles.sum() / 256 + 16
+
+
+@pytest.mark.parametrize("heads,prefix,chunk", [
+    ((24, 4, 64), range(300, 6300, 500), range(40, 1480, 120)),        # 12 requests, 48 streams of all sizes
+    ((16, 16, 128), range(500, 8500, 1000), range(2000, 400, -200)),   # 128 streams
+])
+def test_order_keeps_slots_busy(heads, prefix, chunk):
+    """Items per slot are few and the streams differ in size: handed out domain by domain in the plan's
+    order, 32 one-at-a-time workgroups each, the busiest slot's tiles stay within 10 % of the even share and
+    one item."""
+    import heapq
+    Hq, Hkv, d = heads
+    spec = wl.custom_wave(Hq, Hkv, d, d, 16, list(prefix), list(chunk), seed=5)
+    p = wp.plan_for(spec)
+    it = p.items()
+    coverage_check(spec, it, p.info()["kv_tile"])
+    tiles = -(-(it[:, 5] - it[:, 4]) // p.info()["kv_tile"]) + 1
+    tiles[it[:, 3] == 0] = 0
+    busiest = 0
+    for x in range(8):
+        busy = [0] * 32
+        for t in tiles[x::8]:
+            heapq.heapreplace(busy, busy[0] + int(t))
+        busiest = max(busiest, max(busy))
+    assert busiest <= 1.1 * tiles.sum() / 256 + 2, (busiest, tiles.sum() / 256)
