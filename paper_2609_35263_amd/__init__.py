@@ -66,9 +66,8 @@ class _Shape(ctypes.Structure):
 
 
 class _Batch(ctypes.Structure):
-    _fields_ = [("num_requests", ctypes.c_int32), ("prefix_lens", ctypes.POINTER(ctypes.c_int32)),
-                ("chunk_lens", ctypes.POINTER(ctypes.c_int32)), ("block_table", ctypes.POINTER(ctypes.c_int32)),
-                ("bt_stride", ctypes.c_int32)]
+    _fields_ = [("num_requests", ctypes.c_int32), ("prefix_lens", ctypes.c_void_p), ("chunk_lens", ctypes.c_void_p),
+                ("block_table", ctypes.c_void_p), ("bt_stride", ctypes.c_int32)]
 
 
 class _Info(ctypes.Structure):
@@ -198,6 +197,7 @@ class Plan:
     def __init__(self, handle, shape):
         self._h = ctypes.c_void_p(handle)
         self.shape = shape
+        self._buffers = None       # shapes of a call's tensors, made from `shape` on first use
 
     @property
     def handle(self):
@@ -246,15 +246,13 @@ def plan(*, num_q_heads, num_kv_heads, head_dim_qk, head_dim_v, page_size, num_p
         raise ValueError("prefix_lens, chunk_lens and block_table rows must have the same length")
     shape = _Shape(num_q_heads, num_kv_heads, head_dim_qk, head_dim_v, page_size, num_pages, int(bool(kv_shared)),
                    float(softmax_scale))
-    p32 = ctypes.POINTER(ctypes.c_int32)
-    batch = _Batch(int(prefix.shape[0]), prefix.ctypes.data_as(p32), chunk.ctypes.data_as(p32),
-                   bt.ctypes.data_as(p32), int(bt.shape[1]))
+    batch = _Batch(prefix.shape[0], prefix.ctypes.data, chunk.ctypes.data, bt.ctypes.data, bt.shape[1])
     out = ctypes.c_void_p()
     _check(lib.wavepp_attn_plan(ctypes.byref(shape), ctypes.byref(batch), int(max_splits), ctypes.byref(out)))
     return Plan(out.value, dict(num_q_heads=num_q_heads, num_kv_heads=num_kv_heads, head_dim_qk=head_dim_qk,
                                 head_dim_v=head_dim_v, page_size=page_size, num_pages=num_pages,
                                 kv_shared=bool(kv_shared), softmax_scale=float(softmax_scale),
-                                total_tokens=int(chunk.sum())))
+                                total_tokens=int(np.add.reduce(chunk))))
 
 
 def plan_for(spec, max_splits=0) -> Plan:
@@ -269,34 +267,48 @@ def plan_for(spec, max_splits=0) -> Plan:
 # Device calls (torch tensors for memory and the current stream)
 # ------------------------------------------------------------------------------------------------
 
+# These calls run once per layer of a wave, and on a small wave the host is what takes the time: device
+# pointers go to the library as plain integers, the expected shapes are made once per plan, and a tensor's
+# shape is compared once.
+
+_bf16 = _f32 = None
+
+
+def _dtypes():
+    global _bf16, _f32
+    if _bf16 is None:
+        import torch
+        _bf16, _f32 = torch.bfloat16, torch.float32
+    return _bf16, _f32
+
+
 def _stream(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        import torch
+        stream = torch.cuda.current_stream()
+    return stream.cuda_stream
 
 
-def _check_shapes(**named):
-    """Every tensor (name=(tensor or None, shape)) has the plan's shape.  Checked for all buffers of
+def _check_shapes(*named):
+    """Every tensor (name, tensor or None, shape) has the plan's shape.  Checked for all buffers of
     a call before anything else: the kernels index every buffer by the plan's sizes, so a tensor of
     any other shape would be read or written out of bounds."""
-    for name, (t, shape) in named.items():
-        if t is not None and tuple(t.shape) != tuple(int(x) for x in shape):
-            raise ValueError(f"{name} has shape {tuple(t.shape)}, the plan needs {tuple(int(x) for x in shape)}")
+    for name, t, shape in named:
+        if t is not None and tuple(t.shape) != shape:
+            raise ValueError(f"{name} has shape {tuple(t.shape)}, the plan needs {shape}")
 
 
-def _ptr(t, dtype=None, name="", shape=None):
-    """Device pointer of a contiguous tensor of the given dtype and shape (None: no buffer)."""
+def _ptr(t, dtype=None, name=""):
+    """Device address of a contiguous tensor of the given dtype (None: no buffer)."""
     if t is None:
-        return ctypes.c_void_p(None)
-    if shape is not None:
-        _check_shapes(**{name: (t, shape)})
+        return None
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def new_workspace(p: Plan, device=None):
@@ -306,68 +318,67 @@ def new_workspace(p: Plan, device=None):
 
 
 def plan_upload(p: Plan, workspace, stream=None):
-    _check(load_library().wavepp_attn_plan_upload(p.handle, _ptr(workspace, name="workspace"),
-                                                  workspace.numel() * workspace.element_size(), _stream(stream)))
+    _check(load_library().wavepp_attn_plan_upload(p.handle, _ptr(workspace, name="workspace"), workspace.nbytes,
+                                                  _stream(stream)))
 
 
 def _attn_shapes(p: Plan) -> dict:
+    if p._buffers is not None:
+        return p._buffers
     s = p.shape
     T, Hq, Hkv = s["total_tokens"], s["num_q_heads"], s["num_kv_heads"]
     P, B, dq, dv = s["num_pages"], s["page_size"], s["head_dim_qk"], s["head_dim_v"]
-    return {"q": (T, Hq, dq), "k_new": (T, Hkv, dq), "v_new": (T, Hkv, dv), "k_pool": (P, Hkv, B, dq),
-            "v_pool": (P, Hkv, B, dv), "out": (T, Hq, dv), "lse": (T, Hq)}
+    p._buffers = {"q": (T, Hq, dq), "k_new": (T, Hkv, dq), "v_new": (T, Hkv, dv), "k_pool": (P, Hkv, B, dq),
+                  "v_pool": (P, Hkv, B, dv), "out": (T, Hq, dv), "lse": (T, Hq)}
+    p._buffers = {name: tuple(int(x) for x in shape) for name, shape in p._buffers.items()}
+    return p._buffers
 
 
 def _shared_kv_none(p: Plan, **bufs):
+    shared = p.shape["kv_shared"]
     for name, t in bufs.items():
-        if p.shape["kv_shared"] and t is not None:
+        if shared and t is not None:
             raise ValueError(f"{name} must be None for a latent (kv_shared) cache")
-        if not p.shape["kv_shared"] and t is None:
+        if not shared and t is None:
             raise ValueError(f"{name} is required")
 
 
 def append_kv(p: Plan, k_new, v_new, k_pool, v_pool, workspace, stream=None):
-    import torch
-    bf = torch.bfloat16
+    bf, _ = _dtypes()
     sh = _attn_shapes(p)
     _shared_kv_none(p, v_new=v_new, v_pool=v_pool)
-    _check_shapes(k_new=(k_new, sh["k_new"]), v_new=(v_new, sh["v_new"]), k_pool=(k_pool, sh["k_pool"]),
-                  v_pool=(v_pool, sh["v_pool"]))
+    _check_shapes(("k_new", k_new, sh["k_new"]), ("v_new", v_new, sh["v_new"]), ("k_pool", k_pool, sh["k_pool"]),
+                  ("v_pool", v_pool, sh["v_pool"]))
     _check(load_library().wavepp_attn_append_kv(
-        p.handle, _ptr(k_new, bf, "k_new", sh["k_new"]), _ptr(v_new, bf, "v_new", sh["v_new"]),
-        _ptr(k_pool, bf, "k_pool", sh["k_pool"]), _ptr(v_pool, bf, "v_pool", sh["v_pool"]),
-        _ptr(workspace, name="workspace"), workspace.numel() * workspace.element_size(), _stream(stream)))
+        p.handle, _ptr(k_new, bf, "k_new"), _ptr(v_new, bf, "v_new"), _ptr(k_pool, bf, "k_pool"),
+        _ptr(v_pool, bf, "v_pool"), _ptr(workspace, name="workspace"), workspace.nbytes, _stream(stream)))
 
 
 def chunked_prefill(p: Plan, q, k_pool, v_pool, out, lse, workspace, stream=None):
-    import torch
-    bf = torch.bfloat16
+    bf, f32 = _dtypes()
     sh = _attn_shapes(p)
     _shared_kv_none(p, v_pool=v_pool)
-    _check_shapes(q=(q, sh["q"]), k_pool=(k_pool, sh["k_pool"]), v_pool=(v_pool, sh["v_pool"]),
-                  out=(out, sh["out"]), lse=(lse, sh["lse"]))
+    _check_shapes(("q", q, sh["q"]), ("k_pool", k_pool, sh["k_pool"]), ("v_pool", v_pool, sh["v_pool"]),
+                  ("out", out, sh["out"]), ("lse", lse, sh["lse"]))
     _check(load_library().wavepp_attn_chunked_prefill(
-        p.handle, _ptr(q, bf, "q", sh["q"]), _ptr(k_pool, bf, "k_pool", sh["k_pool"]),
-        _ptr(v_pool, bf, "v_pool", sh["v_pool"]), _ptr(out, bf, "out", sh["out"]),
-        _ptr(lse, torch.float32, "lse", sh["lse"]), _ptr(workspace, name="workspace"),
-        workspace.numel() * workspace.element_size(), _stream(stream)))
+        p.handle, _ptr(q, bf, "q"), _ptr(k_pool, bf, "k_pool"), _ptr(v_pool, bf, "v_pool"), _ptr(out, bf, "out"),
+        _ptr(lse, f32, "lse"), _ptr(workspace, name="workspace"), workspace.nbytes, _stream(stream)))
 
 
 def chunked_prefill_noalloc(p: Plan, q, k_pool, v_pool, out, lse, k_new=None, v_new=None, stream=None):
     """Append (when k_new is given) and attention with no workspace: the library's static per-GPU
     scratch holds the metadata and split partials.  Calls on one GPU must not overlap."""
-    import torch
-    bf = torch.bfloat16
+    bf, f32 = _dtypes()
     sh = _attn_shapes(p)
     _shared_kv_none(p, v_pool=v_pool)
     if p.shape["kv_shared"] and v_new is not None:
         raise ValueError("v_new must be None for a latent (kv_shared) cache")
-    _check_shapes(q=(q, sh["q"]), k_new=(k_new, sh["k_new"]), v_new=(v_new, sh["v_new"]),
-                  k_pool=(k_pool, sh["k_pool"]), v_pool=(v_pool, sh["v_pool"]), out=(out, sh["out"]),
-                  lse=(lse, sh["lse"]))
+    _check_shapes(("q", q, sh["q"]), ("k_new", k_new, sh["k_new"]), ("v_new", v_new, sh["v_new"]),
+                  ("k_pool", k_pool, sh["k_pool"]), ("v_pool", v_pool, sh["v_pool"]), ("out", out, sh["out"]),
+                  ("lse", lse, sh["lse"]))
     _check(load_library().wavepp_attn_chunked_prefill_noalloc(
         p.handle, _ptr(q, bf, "q"), _ptr(k_new, bf, "k_new"), _ptr(v_new, bf, "v_new"), _ptr(k_pool, bf, "k_pool"),
-        _ptr(v_pool, bf, "v_pool"), _ptr(out, bf, "out"), _ptr(lse, torch.float32, "lse"), _stream(stream)))
+        _ptr(v_pool, bf, "v_pool"), _ptr(out, bf, "out"), _ptr(lse, f32, "lse"), _stream(stream)))
 
 
 # ------------------------------------------------------------------------------------------------
@@ -433,27 +444,25 @@ def kda_plan_for(spec) -> KdaPlan:
 
 
 def kda_upload(p: KdaPlan, workspace, stream=None):
-    _check(load_library().wavepp_kda_upload(p.handle, _ptr(workspace, name="workspace"),
-                                            workspace.numel() * workspace.element_size(), _stream(stream)))
+    _check(load_library().wavepp_kda_upload(p.handle, _ptr(workspace, name="workspace"), workspace.nbytes,
+                                            _stream(stream)))
 
 
 def kda_chunked_prefill(p: KdaPlan, q, k, v, alpha, beta, state_pool, out, workspace, stream=None):
-    import torch
-    bf, f32 = torch.bfloat16, torch.float32
+    bf, f32 = _dtypes()
     s = p.shape
     T, H, dk, dv = s["total_tokens"], s["num_heads"], s["head_dim_k"], s["head_dim_v"]
     for name, t in (("q", q), ("k", k), ("v", v), ("alpha", alpha), ("beta", beta), ("state_pool", state_pool),
                     ("out", out)):
         if t is None:
             raise ValueError(f"{name} is required")
-    _check_shapes(q=(q, (T, H, dk)), k=(k, (T, H, dk)), v=(v, (T, H, dv)), alpha=(alpha, (T, H, dk)),
-                  beta=(beta, (T, H)), state_pool=(state_pool, (s["num_state_slots"], H, dk, dv)),
-                  out=(out, (T, H, dv)))
+    _check_shapes(("q", q, (T, H, dk)), ("k", k, (T, H, dk)), ("v", v, (T, H, dv)), ("alpha", alpha, (T, H, dk)),
+                  ("beta", beta, (T, H)), ("state_pool", state_pool, (s["num_state_slots"], H, dk, dv)),
+                  ("out", out, (T, H, dv)))
     _check(load_library().wavepp_kda_chunked_prefill(
-        p.handle, _ptr(q, bf, "q", (T, H, dk)), _ptr(k, bf, "k", (T, H, dk)), _ptr(v, bf, "v", (T, H, dv)),
-        _ptr(alpha, f32, "alpha", (T, H, dk)), _ptr(beta, f32, "beta", (T, H)),
-        _ptr(state_pool, f32, "state_pool", (s["num_state_slots"], H, dk, dv)), _ptr(out, bf, "out", (T, H, dv)),
-        _ptr(workspace, name="workspace"), workspace.numel() * workspace.element_size(), _stream(stream)))
+        p.handle, _ptr(q, bf, "q"), _ptr(k, bf, "k"), _ptr(v, bf, "v"), _ptr(alpha, f32, "alpha"),
+        _ptr(beta, f32, "beta"), _ptr(state_pool, f32, "state_pool"), _ptr(out, bf, "out"),
+        _ptr(workspace, name="workspace"), workspace.nbytes, _stream(stream)))
 
 
 # ------------------------------------------------------------------------------------------------
