@@ -162,3 +162,33 @@ def test_kda_many_single_token_requests():
 def test_kda_many_heads():
     spec = wk.custom(96, 128, 128, [70, 5], [-1, 1], [0, 2], 3)
     _check_custom(spec, wk.make_tensors(spec, seed=112), "96 heads")
+
+
+@pytest.mark.parametrize("heads,lens", [
+    (1, [1]),                                   # one workgroup, one block
+    (43, [64, 128, 1, 65, 200, 63]),            # 258 chains: two workgroups take a second one, in reverse order
+    (96, [130, 70, 64, 33, 5, 1, 192]),         # 672 chains, a part of the third round
+])
+def test_kda_chains_per_workgroup(heads, lens):
+    """More chains than resident workgroups, of one to four blocks: every chain starts from its own snapshot
+    (or none) and leaves its own, whatever its workgroup ran before."""
+    R = len(lens)
+    spec = wk.custom(heads, 128, 128, lens, [i if i % 3 else -1 for i in range(R)], [R + i for i in range(R)], 2 * R)
+    _check_custom(spec, wk.make_tensors(spec, seed=120 + heads), f"{heads} heads, {R} requests")
+
+
+@pytest.mark.parametrize("extreme", [False, True])
+def test_kda_correlated_keys(extreme):
+    """Keys of nearly one direction and write strengths near 1: the triangular inverse is far from the identity
+    in every 8-, 16- and 32-row block; with slow channels (decays of exactly 0) in some blocks only."""
+    spec = wk.custom(3, 128, 128, [64, 200, 97], [-1, 0, 1], [2, 3, 4], 5)
+    t = wk.make_tensors(spec, seed=130)
+    k = t["k"].float()
+    base = torch.randn(1, 3, 128, generator=torch.Generator().manual_seed(4))
+    base = base / base.norm(dim=-1, keepdim=True)
+    k = 0.95 * base + 0.31 * k
+    t["k"] = (k / k.norm(dim=-1, keepdim=True)).to(torch.bfloat16)
+    t["beta"].fill_(0.97)
+    if extreme:
+        t["alpha"][70:90, :, :40] = 0.0
+    _check_custom(spec, t, "correlated keys")
