@@ -73,7 +73,7 @@ typedef struct wavepp_kda_plan_s wavepp_kda_plan_t;
 
 typedef struct {
   int64_t total_tokens;      /* T */
-  int32_t num_items;         /* requests with c_r > 0; the kernel runs one workgroup per (item, head) */
+  int32_t num_items;         /* requests with c_r > 0; the kernel runs one chain of blocks per (item, head) */
   int32_t block_tokens;      /* tokens per block of the chunkwise form (64) */
   int64_t metadata_bytes;
   int64_t workspace_bytes;

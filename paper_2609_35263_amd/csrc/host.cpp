@@ -309,6 +309,69 @@ double split_cost(const std::vector<int64_t>& ntiles, const SplitPlan& sp, int s
   return clock.longest() + merge * partials;
 }
 
+// Modelled time of a small grouped wave in the 8-wave form (attention and merge, microseconds), its key
+// ranges cut evenly into at most `target` items of at least `min_keys` keys: pieces are handed out longest first
+// to 256 workgroups that run one at a time, or the wave streams its K/V at about 5.2 TB/s if that takes longer,
+// and the partials are written and merged.  The constants are fitted to 1,200 timed waves of 1-16 requests,
+// 1K-40K cached tokens and 90-4,000 rows per KV head, 0 to 16 forced splits; the mean error is 4-6 %.  A tile of
+// which only some waves have rows takes `idle` of its time plus the rest by the share of active waves.
+struct GroupedModel {
+  int rows, tile, slots;
+  double idle, overhead, tile_us, base_us, part_us_per_mb, merge_us;
+};
+constexpr GroupedModel kModel128 = {kGqaRowsPerItem, kKvTile, kNumCu, 0.5, 1.0, 2.99, 1.2, 0.55, 2.1};
+constexpr GroupedModel kModel64 = {kGqaRowsPerItem, kKvTile, kNumCu, 0.5, 1.0, 2.08, -3.0, 0.53, 6.7};
+
+double grouped_cost(const wavepp_attn_shape& s, const wavepp_batch& b, int64_t target,
+                    int64_t min_keys) {
+  const GroupedModel& f = s.head_dim_qk == 64 ? kModel64 : kModel128;
+  struct Group { int64_t tiles, count, rows; };       // row tiles of one request that see the same key tiles
+  const int64_t G = s.num_q_heads / s.num_kv_heads, min_tiles = min_keys / f.tile;
+  std::vector<Group> groups;
+  double kv_mb = 0.0;
+  int64_t longest = 1;
+  for (int32_t r = 0; r < b.num_requests; ++r) {
+    const int64_t p = b.prefix_lens[r], c = b.chunk_lens[r], rows = c * G;
+    if (c == 0) continue;
+    const int64_t n = ceil_div(p + c, f.tile);
+    longest = std::max(longest, n);
+    if (rows / f.rows) groups.push_back({n, rows / f.rows * s.num_kv_heads, f.rows});
+    if (rows % f.rows) groups.push_back({n, s.num_kv_heads, rows % f.rows});
+    kv_mb += double(p + c) * s.num_kv_heads * s.head_dim_qk * 4e-6;
+  }
+  auto splits = [&](int64_t n, int64_t T) { return std::max<int64_t>(1, std::min(ceil_div(n, T), n / min_tiles)); };
+  auto total = [&](int64_t T) {
+    int64_t n = 0;
+    for (const Group& g : groups) n += g.count * splits(g.tiles, T);
+    return n;
+  };
+  int64_t lo = std::max<int64_t>(1, min_tiles), hi = std::max(lo, longest);
+  if (total(lo) > target) {
+    while (hi - lo > 1) {
+      const int64_t mid = lo + (hi - lo) / 2;
+      if (total(mid) <= target) hi = mid; else lo = mid;
+    }
+    lo = hi;
+  }
+  std::vector<std::pair<double, int64_t>> pieces;     // (time in tiles, count)
+  double part_mb = 0.0;
+  for (const Group& g : groups) {
+    const int64_t tps = ceil_div(g.tiles, splits(g.tiles, lo)), S = ceil_div(g.tiles, tps);
+    const double w = f.idle + (1.0 - f.idle) * double(ceil_div(g.rows, 32) * 32) / f.rows;
+    if (S > 1) {
+      pieces.push_back({double(tps) * w + f.overhead, g.count * (S - 1)});
+      part_mb += double(g.count * S * g.rows) * s.head_dim_v * 4e-6;
+    }
+    pieces.push_back({double(g.tiles - tps * (S - 1)) * w + f.overhead, g.count});
+  }
+  std::sort(pieces.begin(), pieces.end(), std::greater<std::pair<double, int64_t>>());
+  SlotClock clock(f.slots);
+  for (const auto& x : pieces)
+    for (int64_t i = 0; i < x.second; ++i) clock.add(x.first);
+  return std::max(f.tile_us * clock.longest() + f.base_us, 0.19 * kv_mb) + f.part_us_per_mb * part_mb +
+         (part_mb > 0.0 ? f.merge_us : 0.0);
+}
+
 }  // namespace
 
 namespace wavepp {
@@ -597,7 +660,15 @@ int wavepp_attn_plan(const wavepp_attn_shape* shape, const wavepp_batch* batch, 
       }
       return sp;
     };
-    split = even(fill_target);
+    // The 8-wave grouped form also runs one workgroup per CU; a wave split to 512 items is two rounds of it.  Its
+    // 256 slots are filled once where the model gives that more than 5 %, its mean error: 1.03 to 1.28 times
+    // faster wherever it says so on the timed waves (one request of 8K-40K cached tokens, 64/8 heads, 304 rows
+    // per KV head: 67.5 us as 352 items, 54.6 as 256), while 256 items always would lose 15 % on average.
+    int64_t target = fill_target;
+    if (!mla && !small_rows && int64_t(base.size()) < kNumCu && longest >= 2 * min_split_tiles &&
+        grouped_cost(s, *batch, kNumCu, 1024) < 0.95 * grouped_cost(s, *batch, fill_target, 1024))
+      target = kNumCu;
+    split = even(target);
     // The latent form runs one workgroup per CU: 256 slots, not 512, and its partials are four times as wide.
     // For it the alternatives are even splits of at most 256 items, and pieces of about the mean load per
     // slot: whole pieces fill most slots and the items' remainders pair up on the others.  The cheapest by

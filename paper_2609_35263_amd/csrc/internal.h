@@ -90,7 +90,7 @@ struct alignas(16) KdaHeader {
   int32_t num_heads;
 };
 
-// One request of the wave with at least one token; a workgroup runs one (item, head).
+// One request of the wave with at least one token; a chain of blocks is one (item, head).
 struct alignas(16) KdaItem {
   int32_t req;
   int32_t cu;         // first packed token

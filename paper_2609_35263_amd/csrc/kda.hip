@@ -36,8 +36,13 @@
 //     rows a lane holds for one MFMA are its contraction slots, and the A operand is read from LDS in
 //     that same (permuted) order.
 // Every step of either part is a latency chain (LDS round trips, short dependent products), so two
-// waves per SIMD in different parts hide each other's waits.  A period has six workgroup barriers
-// (more with slow channels); both loops below pass each of them once per block built:
+// waves per SIMD in different parts hide each other's waits.  A wave of 4 x 64 heads x 4,096 tokens:
+// 510 us with four waves that ran the parts in turn, 365 us now, 4.5 TB/s of the 4.9 a plain copy
+// reaches; with 64 chains on 256 CUs (one 16,384-token request) it is the builders' chain, 10.7 K
+// cycles a block, that bounds it (1,951 -> 1,144 us).  All eight waves in the scaling phase, the P tiles
+// given to the runners, and the next block's loads anywhere but row by row in the scaling phase were
+// slower.  A period has six workgroup barriers (more with slow channels); both loops below pass each of
+// them once per block built:
 //     barrier      builders (block n + 1)                   runners (block n)
 //     .. 1         octet decay products
 //     .. 2         Q~, K~, K_R, Kbar of the block           U = T R, O += P U, state update
@@ -486,7 +491,7 @@ __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, co
     // split over the four waves.  A 16x16 accumulator (lane group g holds rows 4g + r) is the B operand
     // of the next product when its contraction slots are taken in that order.  The phase is a latency
     // chain, so the steps are few and wide: substitution over all 16 rows and the 16 -> 32 sums on the
-    // VALU took 7,400 of a block's 23,600 cycles (4 x 64-head wave of 4,096 tokens: 588 us, then 510).
+    // VALU took 7,400 cycles a block, this 2,700 (4 x 64 heads x 4,096 tokens: 588 us, then 510).
     {
       const int a0 = 16 * wave, n16 = lane & 15, g16 = lane >> 4;
       const float* ab = &ls.a[a0 * AS + a0];

@@ -57,7 +57,9 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // wave, at most 256).  The token's request and page are uniform across the workgroup, so they are
 // looked up once, with scalar loads through the constant address space (the kernel never writes the
 // metadata).  A small wave is a chain of dependent loads (request, page, then the store), so it takes
-// one token per workgroup (launch_append), and the rows to be moved are loaded before the lookup.
+// one token per workgroup (launch_append), and the rows to be moved are loaded before the lookup: 128
+// tokens of 8 heads x 128 + 128 took 9 us as 16 workgroups of eight, about 5 us so (a 16-token-chunk layer
+// 181.4 -> 177.0 us).
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ T const_load(const T* ptr) {

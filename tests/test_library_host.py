@@ -473,3 +473,26 @@ def test_order_keeps_slots_busy(heads, prefix, chunk):
             heapq.heapreplace(busy, busy[0] + int(t))
         busiest = max(busiest, max(busy))
     assert busiest <= 1.1 * tiles.sum() / 256 + 2, (busiest, tiles.sum() / 256)
+
+
+@pytest.mark.parametrize("prefix,chunk,once", [
+    ([20000], [38], True),            # one request: 256 pieces, one round of the 256 slots
+    ([20000], [100], None),           # either way, covered once
+    ([9000] * 10, [37] * 10, False),  # 160 base items: 256 would leave them uncut, so two rounds
+])
+def test_grouped_splits_one_or_two_rounds(prefix, chunk, once, monkeypatch):
+    """8-wave form, fewer than 256 base items: split to 256 or to 512 items, whichever is modelled faster;
+    every visible pair is covered once and every piece but an item's last spans at least 1,024 keys."""
+    monkeypatch.delenv("WAVEPP_GQA_WAVES", raising=False)
+    spec = wl.custom_wave(64, 8, 128, 128, 64, prefix, chunk, seed=8)
+    p = wp.plan_for(spec)
+    it = p.items()
+    coverage_check(spec, it, 128)
+    real = it[it[:, 3] > 0]
+    assert p.info()["rows_per_item"] == 256 and len(real) <= 512
+    if once is not None:
+        assert (len(real) <= 256) == once, len(real)
+    last = {}
+    for r in real:
+        last[tuple(r[:3])] = max(last.get(tuple(r[:3]), 0), int(r[7]))
+    assert all(r[5] - r[4] >= 1024 for r in real if r[7] < last[tuple(r[:3])])
