@@ -475,6 +475,21 @@ def test_order_keeps_slots_busy(heads, prefix, chunk):
     assert busiest <= 1.1 * tiles.sum() / 256 + 2, (busiest, tiles.sum() / 256)
 
 
+@pytest.mark.parametrize("heads,prefix,chunk", [
+    ((128, 1, 576, 512, True), [16000] * 8, [1024] * 8),   # 8 latent requests of the same lengths
+    ((64, 8, 128, 128, False), [30000], [4096]),           # one request, 8 KV heads
+])
+def test_equal_streams_keep_one_domain_each(heads, prefix, chunk):
+    """Streams too few to be placed whole and of the same lengths: their equal items come in turn, so every
+    (request, KV head) is read by the workgroups of one domain (dispatch index modulo 8) only."""
+    Hq, Hkv, dk, dv, shared = heads
+    spec = wl.custom_wave(Hq, Hkv, dk, dv, 64, prefix, chunk, seed=6, kv_shared=shared)
+    it = wp.plan_for(spec).items()
+    assert len(it) > 512
+    for x in range(8):
+        assert len({tuple(r[:2]) for r in it[x::8].tolist() if r[3] > 0}) == 1
+
+
 @pytest.mark.parametrize("prefix,chunk,once", [
     ([20000], [38], True),            # one request: 256 pieces, one round of the 256 slots
     ([20000], [100], None),           # either way, covered once
