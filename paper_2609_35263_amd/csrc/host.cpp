@@ -484,6 +484,7 @@ DevPlan make_dev(const wavepp_plan* plan, void* ws) {
   d.num_requests = plan->num_requests;
   d.num_items = int32_t(plan->items.size());
   d.num_merge = int32_t(plan->merges.size());
+  d.max_splits = plan->max_splits_used;
   d.total_tokens = plan->total_tokens;
   d.num_q_heads = plan->shape.num_q_heads;
   d.num_kv_heads = plan->shape.num_kv_heads;

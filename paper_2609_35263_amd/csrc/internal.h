@@ -74,6 +74,7 @@ struct DevPlan {
   int32_t num_q_heads, num_kv_heads, head_dim_qk, head_dim_v, page_size, kv_shared;
   int32_t rows_per_item;   // query rows per attention workgroup (32 per wave)
   float softmax_scale;
+  int32_t max_splits;      // most key-range splits of one item
 };
 
 // ---------------------------------------------------------------------------------------------

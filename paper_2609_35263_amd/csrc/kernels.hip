@@ -875,8 +875,34 @@ __global__ __launch_bounds__(256) void upload_kernel(const u32x4* __restrict__ s
 
 // ---------------------------------------------------------------------------------------------
 // Merge of key-range splits: o = sum_s w_s o_s / sum_s w_s with w_s = exp(lse_s - max lse),
-// lse = max + ln sum_s w_s.  Splits are combined in index order, so results are deterministic.
+// lse = max + ln sum_s w_s.  The order of every sum is fixed by the split count, so results are
+// deterministic.  A split that saw no key has lse = -inf and an all-zero partial row, which gets
+// weight 0.
 // ---------------------------------------------------------------------------------------------
+constexpr int kMergeNarrow = 16;   // most splits of an item that merge_kernel combines
+
+__device__ __forceinline__ float merge_weight(float l, float mx) {
+  return l == -INFINITY ? 0.0f : fast_exp2((l - mx) * kLog2e);
+}
+
+template <int DV>
+__device__ __forceinline__ void merge_store(const DevPlan& p, const MergeItem& mi, int lrow, int c4, f32x4 acc,
+                                            float wsum, float mx, __bf16* out, float* lse_out) {
+  const int Hq = p.num_q_heads, G = Hq / p.num_kv_heads;
+  const float inv = 1.0f / wsum;
+  const int row = mi.row0 + lrow;
+  const int tok = row / G;
+  const int head = mi.kv_head * G + (row - tok * G);
+  bf16x4 o;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) o[k] = static_cast<__bf16>(acc[k] * inv);
+  const int64_t orow = int64_t(p.reqs[mi.req].cu + tok) * Hq + head;
+  *reinterpret_cast<bf16x4*>(out + orow * DV + 4 * c4) = o;
+  if (lse_out && c4 == 0) lse_out[orow] = mx + __logf(wsum);
+}
+
+// Up to kMergeNarrow splits an item: every LSE and partial of a (row, 4 value lanes) is loaded at once by
+// one thread (one memory round trip) and summed in split order.
 template <int DV>
 __global__ __launch_bounds__(256) void merge_kernel(DevPlan p, __bf16* __restrict__ out, float* __restrict__ lse_out) {
   // workgroup (x = merge item, y = row group) handles RPB rows; one thread per (row, 4 value lanes)
@@ -887,13 +913,6 @@ __global__ __launch_bounds__(256) void merge_kernel(DevPlan p, __bf16* __restric
   const int lrow = blockIdx.y * RPB + threadIdx.x / C4;
   const int c4 = threadIdx.x % C4;
   if (lrow >= mi.rows) return;
-  const ReqMeta rm = p.reqs[mi.req];
-  const int Hq = p.num_q_heads, G = Hq / p.num_kv_heads;
-  // The accumulation order is s = 0, 1, ..., nsplit - 1 (deterministic).  A split that saw no key
-  // has lse = -inf and an all-zero partial row, which gets weight 0.  Up to SB splits, every LSE and
-  // partial is loaded at once (one memory round trip); beyond that, two passes read four splits at
-  // a time.  Both paths do the same arithmetic in the same order.
-  constexpr int SB = 16;
   const int ns = mi.nsplit;
   const float* __restrict__ lp = p.lpart + mi.part + lrow;
   const float* __restrict__ op = p.opart + (int64_t(mi.part) + lrow) * DV + 4 * c4;
@@ -901,71 +920,88 @@ __global__ __launch_bounds__(256) void merge_kernel(DevPlan p, __bf16* __restric
   float mx = -INFINITY;
   f32x4 acc = f32x4{};
   float wsum = 0.0f;
-  if (ns <= SB) {
+  float l[kMergeNarrow];
+  f32x4 v[kMergeNarrow];
+#pragma unroll
+  for (int u = 0; u < kMergeNarrow; ++u) {
+    l[u] = u < ns ? lp[u * mi.rows] : -INFINITY;
+    v[u] = u < ns ? *reinterpret_cast<const f32x4*>(op + u * ostep) : f32x4{};
+  }
+#pragma unroll
+  for (int u = 0; u < kMergeNarrow; ++u) mx = fmaxf(mx, l[u]);
+#pragma unroll
+  for (int u = 0; u < kMergeNarrow; ++u) {
+    if (u < ns) {
+      const float w = merge_weight(l[u], mx);
+      acc += w * v[u];
+      wsum += w;
+    }
+  }
+  merge_store<DV>(p, mi, lrow, c4, acc, wsum, mx, out, lse_out);
+}
+
+// Plans with an item of more splits (a few requests behind a long prefix: up to a piece per CU).  Such a wave has
+// few rows, and one thread that walks all splits of its row is a chain of memory round trips (four splits a trip,
+// once for the LSEs and once for the partials).  Here a workgroup takes one row: all its threads load the
+// LSEs for the maximum at once, then SG groups of threads each sum a run of neighbouring splits, eight loads in
+// flight, and the runs are added in order.
+// Attention with the merge, this form against one thread a row: latent, 16 heads, 4 tokens behind 131,072, 228 splits
+// 87 -> 57 us; 16/1 heads of 128, 121 splits 49 -> 32 us; 8/2 of 64, 92 splits 39 -> 26 us; 64/8 of 128, 63
+// splits 120 -> 112 us; the same within 1 % at 17 to 40 splits.  Up to 16, a thread has every load in flight anyway.
+template <int DV>
+__global__ __launch_bounds__(DV == 512 ? 512 : 256) void merge_wide_kernel(DevPlan p, __bf16* __restrict__ out,
+                                                                           float* __restrict__ lse_out) {
+  constexpr int NT = DV == 512 ? 512 : 256;
+  constexpr int C4 = DV / 4, SG = NT / C4, SB = 8;
+  __shared__ float wave_max[NT / 64];
+  __shared__ float run_w[SG];
+  __shared__ f32x4 run_acc[SG][C4];
+  if (!meta_ok(p)) return;
+  const MergeItem mi = p.merges[blockIdx.x];
+  const int lrow = blockIdx.y;
+  if (lrow >= mi.rows) return;
+  const int tid = threadIdx.x, c4 = tid % C4, g = tid / C4;
+  const int ns = mi.nsplit;
+  const float* __restrict__ lp = p.lpart + mi.part + lrow;
+  const float* __restrict__ op = p.opart + (int64_t(mi.part) + lrow) * DV + 4 * c4;
+  const int64_t ostep = int64_t(mi.rows) * DV;
+  float mx = -INFINITY;
+  for (int s = tid; s < ns; s += NT) mx = fmaxf(mx, lp[int64_t(s) * mi.rows]);
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) mx = fmaxf(mx, __shfl_xor(mx, m));
+  if (tid % 64 == 0) wave_max[tid / 64] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NT / 64; ++k) mx = fmaxf(mx, wave_max[k]);
+  f32x4 acc = f32x4{};
+  float wsum = 0.0f;
+  const int run = (ns + SG - 1) / SG;
+  const int end = min(ns, (g + 1) * run);
+  for (int s = g * run; s < end; s += SB) {
     float l[SB];
     f32x4 v[SB];
 #pragma unroll
     for (int u = 0; u < SB; ++u) {
-      l[u] = u < ns ? lp[u * mi.rows] : -INFINITY;
-      v[u] = u < ns ? *reinterpret_cast<const f32x4*>(op + u * ostep) : f32x4{};
+      l[u] = s + u < end ? lp[int64_t(s + u) * mi.rows] : -INFINITY;
+      v[u] = s + u < end ? *reinterpret_cast<const f32x4*>(op + (s + u) * ostep) : f32x4{};
     }
-#pragma unroll
-    for (int u = 0; u < SB; ++u) mx = fmaxf(mx, l[u]);
 #pragma unroll
     for (int u = 0; u < SB; ++u) {
-      if (u < ns) {
-        const float w = (l[u] == -INFINITY) ? 0.0f : fast_exp2((l[u] - mx) * kLog2e);
-        acc += w * v[u];
-        wsum += w;
-      }
-    }
-  } else {
-    {
-      int s = 0;
-      for (; s + 4 <= ns; s += 4) {
-        float l[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) l[u] = lp[(s + u) * mi.rows];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) mx = fmaxf(mx, l[u]);
-      }
-      for (; s < ns; ++s) mx = fmaxf(mx, lp[s * mi.rows]);
-    }
-    {
-      int s = 0;
-      for (; s + 4 <= ns; s += 4) {
-        float l[4];
-        f32x4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          l[u] = lp[(s + u) * mi.rows];
-          v[u] = *reinterpret_cast<const f32x4*>(op + (s + u) * ostep);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const float w = (l[u] == -INFINITY) ? 0.0f : fast_exp2((l[u] - mx) * kLog2e);
-          acc += w * v[u];
-          wsum += w;
-        }
-      }
-      for (; s < ns; ++s) {
-        const float l = lp[s * mi.rows];
-        const float w = (l == -INFINITY) ? 0.0f : fast_exp2((l - mx) * kLog2e);
-        acc += w * *reinterpret_cast<const f32x4*>(op + s * ostep);
-        wsum += w;
-      }
+      const float w = merge_weight(l[u], mx);
+      acc += w * v[u];
+      wsum += w;
     }
   }
-  const float inv = 1.0f / wsum;
-  const int row = mi.row0 + lrow;
-  const int tok = row / G;
-  const int head = mi.kv_head * G + (row - tok * G);
-  bf16x4 o;
+  run_acc[g][c4] = acc;
+  if (c4 == 0) run_w[g] = wsum;
+  __syncthreads();
+  if (g) return;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) o[k] = static_cast<__bf16>(acc[k] * inv);
-  const int64_t orow = int64_t(rm.cu + tok) * Hq + head;
-  *reinterpret_cast<bf16x4*>(out + orow * DV + 4 * c4) = o;
-  if (lse_out && c4 == 0) lse_out[orow] = mx + __logf(wsum);
+  for (int k = 1; k < SG; ++k) {
+    acc += run_acc[k][c4];
+    wsum += run_w[k];
+  }
+  merge_store<DV>(p, mi, lrow, c4, acc, wsum, mx, out, lse_out);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1055,17 +1091,22 @@ hipError_t launch_upload(const void* src, void* dst, size_t bytes, hipStream_t s
 hipError_t launch_merge(const DevPlan& p, void* out, float* lse, hipStream_t stream) {
   if (p.num_merge == 0) return hipSuccess;
   auto oo = static_cast<__bf16*>(out);
-  const int c4 = p.head_dim_v / 4;
-  const int rpb = 256 / c4;
-  const dim3 grid(p.num_merge, (p.rows_per_item + rpb - 1) / rpb), block(256);
-  if (p.head_dim_v == 128)
-    hipLaunchKernelGGL((merge_kernel<128>), grid, block, 0, stream, p, oo, lse);
-  else if (p.head_dim_v == 64)
-    hipLaunchKernelGGL((merge_kernel<64>), grid, block, 0, stream, p, oo, lse);
-  else if (p.head_dim_v == 512)
-    hipLaunchKernelGGL((merge_kernel<512>), grid, block, 0, stream, p, oo, lse);
-  else
-    return hipErrorInvalidValue;
+  const int dv = p.head_dim_v;
+  if (dv != 64 && dv != 128 && dv != 512) return hipErrorInvalidValue;
+  const bool wide = p.max_splits > kMergeNarrow;
+  const int rpb = wide ? 1 : 256 / (dv / 4);
+  const dim3 grid(p.num_merge, (p.rows_per_item + rpb - 1) / rpb), block(wide && dv == 512 ? 512 : 256);
+#define WAVEPP_MERGE(DV_)                                                                      \
+  if (wide) hipLaunchKernelGGL((merge_wide_kernel<DV_>), grid, block, 0, stream, p, oo, lse); \
+  else hipLaunchKernelGGL((merge_kernel<DV_>), grid, block, 0, stream, p, oo, lse);
+  if (dv == 128) {
+    WAVEPP_MERGE(128)
+  } else if (dv == 64) {
+    WAVEPP_MERGE(64)
+  } else {
+    WAVEPP_MERGE(512)
+  }
+#undef WAVEPP_MERGE
   return hipGetLastError();
 }
 
