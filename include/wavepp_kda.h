@@ -79,7 +79,8 @@ typedef struct {
   int64_t workspace_bytes;
 } wavepp_kda_info;
 
-/* Validate the wave and build the work list (longest chunks first).  Host only. */
+/* Validate the wave and build the work list: longest chunks first, and for chunks of unlike lengths the (request,
+ * head) chains that each of the kernel's resident workgroups runs, evened out by length.  Host only. */
 int wavepp_kda_plan(const wavepp_kda_shape* shape, const wavepp_kda_batch* batch, wavepp_kda_plan_t** out);
 
 /* Device workspace the plan needs (metadata only), 256-byte aligned. */

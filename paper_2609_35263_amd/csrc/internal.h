@@ -83,6 +83,7 @@ struct DevPlan {
 constexpr uint32_t kKdaMagic = 0x4B444131u;  // "KDA1"
 constexpr int kKdaBlock = 64;                // tokens per block of the chunkwise form
 constexpr int kKdaDim = 128;                 // d_k = d_v supported by the kernel
+constexpr int64_t kKdaMaxListed = 1 << 20;   // most chains whose workgroups are listed in the metadata (4 MiB)
 
 struct alignas(16) KdaHeader {
   uint32_t magic;
@@ -113,6 +114,9 @@ struct KdaDevPlan {
   int32_t num_items;
   int32_t num_heads;
   int32_t num_slots;
+  // 1: the int32 array `list` after the items holds the chains (item * num_heads + head) of each of the kNumCu
+  // workgroups, w's from list[list[w]] to list[list[w + 1] - 1].  0: the kernel's fixed order.
+  int32_t listed;
 };
 
 hipError_t launch_kda_prefill(const KdaDevPlan& p, const void* q, const void* k, const void* v, const float* alpha,

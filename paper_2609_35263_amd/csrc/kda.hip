@@ -160,21 +160,46 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const __bf16* p) {
 // operations before the barrier is enough.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Position in a workgroup's run: block [blk, blk + 64) of one (request, head) chain.  Workgroup w of G
-// takes chains w, 2G - 1 - w, 2G + w, ... of the list (longest chunks first), so that the loads even out.
+template <typename T>
+__device__ __forceinline__ T const_load(const T* ptr) {
+  // scalar load: the metadata is never written by this kernel
+  return *((const __attribute__((address_space(4))) T*)(ptr));
+}
+
+// Position in a workgroup's run: block [blk, blk + 64) of one (request, head) chain.  Chains of unlike lengths are
+// listed by workgroup after the items, by load (kListed); of like ones workgroup w of G takes chains w, 2G - 1 - w,
+// 2G + w, ...  Two kernels: a single-block launch takes 0.4 us longer with the choice made in the kernel.
+template <bool kListed>
 struct Cursor {
-  int round = 0, blk = 0, head = 0;
+  int round = 0, end = 0;        // place of the chain in the list and the end of the workgroup's part; or its round
+  int blk = 0, head = 0;
   int cu = 0, len = 0, state_in = -1, state_out = -1;   // of the chain's item
   bool valid = false;
 
+  static __device__ __forceinline__ const int32_t* list(const KdaDevPlan& p) {
+    return reinterpret_cast<const int32_t*>(p.items + p.num_items);
+  }
+  __device__ __forceinline__ void start(const KdaDevPlan& p) {
+    if (kListed) {
+      round = const_load(list(p) + blockIdx.x);
+      end = const_load(list(p) + blockIdx.x + 1);
+    }
+    open(p);
+  }
   __device__ __forceinline__ void open(const KdaDevPlan& p) {
-    const int G = gridDim.x;
-    const int c = round * G + ((round & 1) ? G - 1 - int(blockIdx.x) : int(blockIdx.x));
-    valid = c < p.num_items * p.num_heads;
-    if (!valid) return;
+    int c;
+    if (kListed) {
+      valid = round < end;
+      if (!valid) return;
+      c = const_load(list(p) + round);
+    } else {
+      const int G = gridDim.x;
+      c = round * G + ((round & 1) ? G - 1 - int(blockIdx.x) : int(blockIdx.x));
+      valid = c < p.num_items * p.num_heads;
+      if (!valid) return;
+    }
     const int item = c / p.num_heads;
     head = c - item * p.num_heads;
-    // scalar loads: the metadata is never written by this kernel
     const auto* it = (const __attribute__((address_space(4))) KdaItem*)(p.items + item);
     cu = it->cu;
     len = it->len;
@@ -212,8 +237,9 @@ struct RawLoader {
   const float* b;
   int rows, brows;               // rows left of this thread's octet, of the block from this thread's beta row on
 
+  template <bool kListed>
   __device__ __forceinline__ void open(const float* alpha, const __bf16* kp, const __bf16* qp, const float* beta,
-                                       const Cursor& c, int H, int tid) {
+                                       const Cursor<kListed>& c, int H, int tid) {
     const int cq = tid & 31, oc = tid >> 5;
     const int64_t at = (c.tok0() + 8 * oc) * (int64_t(H) * kD) + int64_t(c.head) * kD + 4 * cq;
     a = alpha + at;
@@ -243,6 +269,7 @@ __device__ __forceinline__ int kbt_at(int c, int t) { return c * CS + (t ^ ((c >
 // Fence for the scheduler: reads, products and stores stay on their side, ALU work may cross.
 __device__ __forceinline__ void keep_order() { __builtin_amdgcn_sched_barrier(0x6); }
 
+template <bool kListed>
 __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, const __bf16* __restrict__ q,
                                              const __bf16* __restrict__ k, const float* __restrict__ alpha,
                                              const float* __restrict__ beta, int wave, int tid) {
@@ -250,8 +277,8 @@ __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, co
   const int H = p.num_heads;
   const int64_t tok_stride = int64_t(H) * kD;           // elements between tokens of one head
   const int cq = tid & 31, oc = tid >> 5;               // channels 4 cq + e, tokens 8 oc + i
-  Cursor cur;
-  cur.open(p);
+  Cursor<kListed> cur;
+  cur.start(p);
   RawBlock raw;
   RawLoader ld;
   ld.open(alpha, k, q, beta, cur, H, tid);
@@ -262,7 +289,7 @@ __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, co
     const int L = cur.rows();
     const int64_t tok0 = cur.tok0();
     const int64_t head_off = int64_t(cur.head) * kD;
-    Cursor nxt = cur;
+    Cursor<kListed> nxt = cur;
     nxt.advance(p);
 
     // ---- decays -------------------------------------------------------------------------------
@@ -589,6 +616,7 @@ __device__ __forceinline__ void build_blocks(const KdaDevPlan& p, KdaLds& ls, co
   }
 }
 
+template <bool kListed>
 __device__ __forceinline__ void run_blocks(const KdaDevPlan& p, KdaLds& ls, const __bf16* __restrict__ v,
                                            float* __restrict__ state_pool, __bf16* __restrict__ out, int wave, int lane) {
   const int col = lane & 31, hf = lane >> 5;
@@ -598,8 +626,8 @@ __device__ __forceinline__ void run_blocks(const KdaDevPlan& p, KdaLds& ls, cons
   const int mrow = lane >> 2, mpart = 8 * (lane & 3);   // 16-byte moves of V: rows mrow + 16 i
   const int64_t v_lane = mrow * tok_stride + j0 + mpart, o_lane = col * tok_stride + j0 + 8 * hf;
   __bf16* vt = ls.vt[wave];
-  Cursor cur, nxt;
-  nxt.open(p);
+  Cursor<kListed> cur, nxt;
+  nxt.start(p);
   // state tile ib, register 4b + r: row i = 32 ib + 8 b + 4 hf + r, column j0 + col
   f32x16 S[4], accE[2], accO[2];
   bf16x8 uB[2][2];
@@ -769,6 +797,7 @@ __device__ __forceinline__ void run_blocks(const KdaDevPlan& p, KdaLds& ls, cons
   }
 }
 
+template <bool kListed>
 __global__ __launch_bounds__(512, 2) void kda_prefill_kernel(KdaDevPlan p, const __bf16* __restrict__ q,
                                                              const __bf16* __restrict__ k,
                                                              const __bf16* __restrict__ v,
@@ -785,9 +814,9 @@ __global__ __launch_bounds__(512, 2) void kda_prefill_kernel(KdaDevPlan p, const
       ls.tm[(32 * h + (tid >> 4)) * CS + 32 * h + 16 + (tid & 15)] = static_cast<__bf16>(0.0f);
   // (ordered before their first reader by the period's barriers)
   if (wave < 4)
-    build_blocks(p, ls, q, k, alpha, beta, wave, tid);
+    build_blocks<kListed>(p, ls, q, k, alpha, beta, wave, tid);
   else
-    run_blocks(p, ls, v, state_pool, out, wave - 4, tid & 63);
+    run_blocks<kListed>(p, ls, v, state_pool, out, wave - 4, tid & 63);
 }
 
 }  // namespace
@@ -796,9 +825,9 @@ hipError_t launch_kda_prefill(const KdaDevPlan& p, const void* q, const void* k,
                               const float* beta, float* state_pool, void* out, hipStream_t stream) {
   if (p.num_items == 0) return hipSuccess;
   const dim3 grid(std::min(p.num_items * p.num_heads, kNumCu)), block(512);
-  hipLaunchKernelGGL(kda_prefill_kernel, grid, block, 0, stream, p, static_cast<const __bf16*>(q),
-                     static_cast<const __bf16*>(k), static_cast<const __bf16*>(v), alpha, beta, state_pool,
-                     static_cast<__bf16*>(out));
+  hipLaunchKernelGGL(p.listed ? kda_prefill_kernel<true> : kda_prefill_kernel<false>, grid, block, 0, stream, p,
+                     static_cast<const __bf16*>(q), static_cast<const __bf16*>(k), static_cast<const __bf16*>(v), alpha,
+                     beta, state_pool, static_cast<__bf16*>(out));
   return hipGetLastError();
 }
 

@@ -24,6 +24,7 @@ struct wavepp_kda_plan_s {
   std::vector<KdaItem> items;
   std::vector<unsigned char> blob;
   size_t off_items = 0;
+  bool listed = false;   // each workgroup's chains follow the items
   size_t workspace_bytes = 0;
 };
 
@@ -37,6 +38,47 @@ int check_ws(const wavepp_kda_plan_t* plan, void* ws, size_t ws_bytes) {
   if (ws_bytes < plan->workspace_bytes)
     return set_error(WAVEPP_ENOSPACE, "workspace has %zu bytes, plan needs %zu", ws_bytes, plan->workspace_bytes);
   return WAVEPP_OK;
+}
+
+// Which of the kernel's kNumCu resident workgroups runs each chain: longest first, each to the workgroup with
+// the least work so far, as the hardware hands out workgroups of one chain.  A fixed order that gives every workgroup
+// a chain of each round, whatever it has, is 1.3 to 1.5 times slower on waves of one long prompt beside many
+// short ones: 1 x 4,096 and 63 x 512 tokens, 32 heads: 120 blocks on the busiest workgroup, 600 us, against 72
+// and 438-448; 1 x 8,192 and 255 x 512, 16 heads: 1,220 us against 830-850.  A chain costs its blocks and about
+// half a block for its snapshots (16 chains of 4 blocks a workgroup take 411 us, one of 64 blocks 369).
+// Empty where the fixed order is as good: at most one chain a workgroup, or all of the same number of blocks (64
+// requests of one token, 64 heads: 114 us in the fixed order, 133 listed); and beyond kKdaMaxListed chains,
+// thousands a workgroup, where its imbalance is small but for a chain as long as many.  Listing takes about 5 ns
+// a chain.
+// The chains of `items` (longest first) come in runs of equal length.  Within a run the workgroups' new loads
+// only grow, so the least loaded one is at the head of one of two sorted queues: no heap.
+std::vector<int32_t> chain_owners(const std::vector<KdaItem>& items, int heads) {
+  std::vector<int32_t> owner;
+  auto blocks = [&](size_t i) { return int64_t(items[i].len + kKdaBlock - 1) / kKdaBlock; };
+  const int64_t chains = int64_t(items.size()) * heads;
+  if (chains <= kNumCu || chains > kKdaMaxListed || blocks(0) == blocks(items.size() - 1)) return owner;
+  owner.resize(size_t(chains));
+  typedef std::pair<int64_t, int32_t> Load;           // (work, workgroup)
+  std::vector<Load> ready, given, rest;
+  given.reserve(size_t(chains));
+  for (int32_t w = 0; w < kNumCu; ++w) ready.push_back(Load(0, w));
+  int64_t c = 0;
+  for (size_t i = 0, j; i < items.size(); i = j) {
+    for (j = i + 1; j < items.size() && blocks(j) == blocks(i);) ++j;
+    const int64_t cost = 2 * blocks(i) + 1, end = int64_t(j) * heads;
+    size_t r = 0, g = 0;
+    given.clear();
+    for (; c < end; ++c) {
+      const bool old = r < ready.size() && (g == given.size() || ready[r].first <= given[g].first);
+      const Load least = old ? ready[r++] : given[g++];
+      owner[size_t(c)] = least.second;
+      given.push_back(Load(least.first + cost, least.second));
+    }
+    rest.clear();
+    std::merge(ready.begin() + r, ready.end(), given.begin() + g, given.end(), std::back_inserter(rest));
+    ready.swap(rest);
+  }
+  return owner;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -106,7 +148,7 @@ int wavepp_kda_plan(const wavepp_kda_shape* shape, const wavepp_kda_batch* batch
     }
     cu += c;
   }
-  // longest chunks first: workgroups are dispatched in index order
+  // longest chunks first: the order in which chains are given to workgroups
   std::stable_sort(plan->items.begin(), plan->items.end(),
                    [](const KdaItem& a, const KdaItem& b) { return a.len > b.len; });
   if (int64_t(plan->items.size()) * s.num_heads > INT32_MAX / 2) {
@@ -114,7 +156,23 @@ int wavepp_kda_plan(const wavepp_kda_shape* shape, const wavepp_kda_batch* batch
     return set_error(WAVEPP_EINVAL, "too many workgroups");
   }
   plan->off_items = align_up(sizeof(KdaHeader), 16);
-  plan->blob.assign(plan->off_items + sizeof(KdaItem) * plan->items.size(), 0);
+  size_t bytes = plan->off_items + sizeof(KdaItem) * plan->items.size();
+  std::vector<int32_t> list;
+  if (!plan->items.empty()) {
+    const std::vector<int32_t> owner = chain_owners(plan->items, s.num_heads);
+    if (!owner.empty()) {
+      list.assign(kNumCu + 1, 0);
+      for (int32_t w : owner) ++list[size_t(w) + 1];
+      list[0] = kNumCu + 1;
+      for (int w = 0; w < kNumCu; ++w) list[w + 1] += list[w];
+      std::vector<int32_t> at(list);
+      list.resize(list.size() + owner.size());
+      for (size_t c = 0; c < owner.size(); ++c) list[at[owner[c]]++] = int32_t(c);
+      plan->listed = true;
+      bytes = align_up(bytes + sizeof(int32_t) * list.size(), 16);
+    }
+  }
+  plan->blob.assign(bytes, 0);
   KdaHeader h{};
   h.magic = kKdaMagic;
   h.serial = plan->serial;
@@ -123,6 +181,9 @@ int wavepp_kda_plan(const wavepp_kda_shape* shape, const wavepp_kda_batch* batch
   memcpy(plan->blob.data(), &h, sizeof(h));
   if (!plan->items.empty())
     memcpy(plan->blob.data() + plan->off_items, plan->items.data(), sizeof(KdaItem) * plan->items.size());
+  if (!list.empty())
+    memcpy(plan->blob.data() + plan->off_items + sizeof(KdaItem) * plan->items.size(), list.data(),
+           sizeof(int32_t) * list.size());
   plan->workspace_bytes = align_up(plan->blob.size(), 256);
   *out = plan;
   return WAVEPP_OK;
@@ -170,6 +231,7 @@ int wavepp_kda_chunked_prefill(const wavepp_kda_plan_t* plan, const void* q, con
   auto* base = static_cast<unsigned char*>(workspace);
   d.hdr = reinterpret_cast<const KdaHeader*>(base);
   d.items = reinterpret_cast<const KdaItem*>(base + plan->off_items);
+  d.listed = plan->listed;
   d.serial = plan->serial;
   d.num_items = int32_t(plan->items.size());
   d.num_heads = plan->shape.num_heads;

@@ -166,8 +166,10 @@ def test_kda_many_heads():
 
 @pytest.mark.parametrize("heads,lens", [
     (1, [1]),                                   # one workgroup, one block
-    (43, [64, 128, 1, 65, 200, 63]),            # 258 chains: two workgroups take a second one, in reverse order
-    (96, [130, 70, 64, 33, 5, 1, 192]),         # 672 chains, a part of the third round
+    (43, [64, 128, 1, 65, 200, 63]),            # 258 chains: two workgroups take a second one
+    (96, [130, 70, 64, 33, 5, 1, 192]),         # 672 chains of unlike lengths, by load
+    (43, [64, 60, 1] * 5),      # 645 chains of one block each: fixed order, a part of the third round
+    (8, [700] + [70, 5] * 20),                  # long chains alone on their workgroups, the others share the short ones
 ])
 def test_kda_chains_per_workgroup(heads, lens):
     """More chains than resident workgroups, of one to four blocks: every chain starts from its own snapshot

@@ -7,6 +7,7 @@ launchers, and driven by seeded randomized inputs:
 * address + undefined-behaviour sanitizers over ``tests/native/host_fuzz.cpp`` (every accepted
   attention plan's work list is checked for exact coverage; every status against a restatement of
   the validation rules);
+* the same over ``tests/native/kda_chains.cpp`` (a KDA plan's chains, walked as the kernel's workgroups do);
 * thread sanitizer over ``tests/native/hints_threads.cpp`` (concurrent add / detach / probe of the
   sharded hint index).
 
@@ -57,6 +58,15 @@ def test_host_code_under_address_and_undefined_behaviour_sanitizers():
             out = _run(exe, ["1500", seed], {"ASAN_OPTIONS": "detect_leaks=1:abort_on_error=0",
                                              "UBSAN_OPTIONS": "print_stacktrace=1"})
             assert "host_fuzz ok" in out
+
+
+def test_kda_chains_run_once_and_evenly():
+    with tempfile.TemporaryDirectory() as d:
+        exe = os.path.join(d, "kda_chains")
+        others = [f for f in HOST_SOURCES if not f.endswith("kda_host.cpp")]     # the test includes that one
+        _build(exe, others + [os.path.join(NATIVE, "launch_stubs.cpp"), os.path.join(NATIVE, "kda_chains.cpp")],
+               "address,undefined")
+        assert "kda_chains ok" in _run(exe, [], {"ASAN_OPTIONS": "detect_leaks=1"})
 
 
 def test_hint_index_under_thread_sanitizer():
