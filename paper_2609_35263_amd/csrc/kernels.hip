@@ -886,7 +886,7 @@ __device__ __forceinline__ float merge_weight(float l, float mx) {
 }
 
 template <int DV>
-__device__ __forceinline__ void merge_store(const DevPlan& p, const MergeItem& mi, int lrow, int c4, f32x4 acc,
+__device__ __forceinline__ void merge_store(const DevPlan& p, const MergeItem& mi, int cu, int lrow, int c4, f32x4 acc,
                                             float wsum, float mx, __bf16* out, float* lse_out) {
   const int Hq = p.num_q_heads, G = Hq / p.num_kv_heads;
   const float inv = 1.0f / wsum;
@@ -896,13 +896,15 @@ __device__ __forceinline__ void merge_store(const DevPlan& p, const MergeItem& m
   bf16x4 o;
 #pragma unroll
   for (int k = 0; k < 4; ++k) o[k] = static_cast<__bf16>(acc[k] * inv);
-  const int64_t orow = int64_t(p.reqs[mi.req].cu + tok) * Hq + head;
+  const int64_t orow = int64_t(cu + tok) * Hq + head;
   *reinterpret_cast<bf16x4*>(out + orow * DV + 4 * c4) = o;
   if (lse_out && c4 == 0) lse_out[orow] = mx + __logf(wsum);
 }
 
 // Up to kMergeNarrow splits an item: every LSE and partial of a (row, 4 value lanes) is loaded at once by
-// one thread (one memory round trip) and summed in split order.
+// one thread (one memory round trip) and summed in split order.  Splits that the item does not have are left
+// undefined: a zero in their place once made the compiler wait for the first partial before it asked for the
+// others, 10-12 % of the kernel (128 value lanes, 21 requests in 5 splits: 49 us, 54 with that wait).
 template <int DV>
 __global__ __launch_bounds__(256) void merge_kernel(DevPlan p, __bf16* __restrict__ out, float* __restrict__ lse_out) {
   // workgroup (x = merge item, y = row group) handles RPB rows; one thread per (row, 4 value lanes)
@@ -913,7 +915,7 @@ __global__ __launch_bounds__(256) void merge_kernel(DevPlan p, __bf16* __restric
   const int lrow = blockIdx.y * RPB + threadIdx.x / C4;
   const int c4 = threadIdx.x % C4;
   if (lrow >= mi.rows) return;
-  const int ns = mi.nsplit;
+  const int ns = mi.nsplit, cu = p.reqs[mi.req].cu;
   const float* __restrict__ lp = p.lpart + mi.part + lrow;
   const float* __restrict__ op = p.opart + (int64_t(mi.part) + lrow) * DV + 4 * c4;
   const int64_t ostep = int64_t(mi.rows) * DV;
@@ -924,8 +926,11 @@ __global__ __launch_bounds__(256) void merge_kernel(DevPlan p, __bf16* __restric
   f32x4 v[kMergeNarrow];
 #pragma unroll
   for (int u = 0; u < kMergeNarrow; ++u) {
-    l[u] = u < ns ? lp[u * mi.rows] : -INFINITY;
-    v[u] = u < ns ? *reinterpret_cast<const f32x4*>(op + u * ostep) : f32x4{};
+    l[u] = -INFINITY;
+    if (u < ns) {
+      l[u] = lp[u * mi.rows];
+      v[u] = *reinterpret_cast<const f32x4*>(op + u * ostep);
+    }
   }
 #pragma unroll
   for (int u = 0; u < kMergeNarrow; ++u) mx = fmaxf(mx, l[u]);
@@ -937,7 +942,7 @@ __global__ __launch_bounds__(256) void merge_kernel(DevPlan p, __bf16* __restric
       wsum += w;
     }
   }
-  merge_store<DV>(p, mi, lrow, c4, acc, wsum, mx, out, lse_out);
+  merge_store<DV>(p, mi, cu, lrow, c4, acc, wsum, mx, out, lse_out);
 }
 
 // Plans with an item of more splits (a few requests behind a long prefix: up to a piece per CU).  Such a wave has
@@ -961,7 +966,7 @@ __global__ __launch_bounds__(DV == 512 ? 512 : 256) void merge_wide_kernel(DevPl
   const int lrow = blockIdx.y;
   if (lrow >= mi.rows) return;
   const int tid = threadIdx.x, c4 = tid % C4, g = tid / C4;
-  const int ns = mi.nsplit;
+  const int ns = mi.nsplit, cu = p.reqs[mi.req].cu;
   const float* __restrict__ lp = p.lpart + mi.part + lrow;
   const float* __restrict__ op = p.opart + (int64_t(mi.part) + lrow) * DV + 4 * c4;
   const int64_t ostep = int64_t(mi.rows) * DV;
@@ -1001,7 +1006,7 @@ __global__ __launch_bounds__(DV == 512 ? 512 : 256) void merge_wide_kernel(DevPl
     acc += run_acc[k][c4];
     wsum += run_w[k];
   }
-  merge_store<DV>(p, mi, lrow, c4, acc, wsum, mx, out, lse_out);
+  merge_store<DV>(p, mi, cu, lrow, c4, acc, wsum, mx, out, lse_out);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -1,0 +1,49 @@
+"""The built library's own gfx950 code, read back on the CPU: properties of a kernel's instruction order that its
+speed rests on and that the compiler can lose without any result changing."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+import paper_2609_35263_amd as wp
+
+OBJDUMP = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+
+pytestmark = pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="needs ROCm's llvm-objdump")
+
+
+@pytest.fixture(scope="module")
+def code(tmp_path_factory):
+    """Kernel symbol -> its instructions, in program order."""
+    d = tmp_path_factory.mktemp("code")
+    lib = shutil.copy(wp.LIB_PATH, d / "lib.so")
+    subprocess.run([OBJDUMP, "--offloading", str(lib)], check=True, capture_output=True, cwd=d)
+    kernels, name = {}, None
+    for obj in sorted(d.glob("*gfx950*")):
+        text = subprocess.run([OBJDUMP, "-d", str(obj)], check=True, capture_output=True, text=True).stdout
+        for line in text.splitlines():
+            m = re.match(r"[0-9a-f]+ <(\S+)>:", line)
+            if m:
+                name = m[1]
+                kernels[name] = []
+            elif name and line.startswith("\t"):
+                kernels[name].append(line.split("//")[0].strip())
+    return kernels
+
+
+def _find(code, *parts):
+    names = [n for n in code if all(p in n for p in parts) and not n.endswith(".kd")]
+    assert len(names) == 1, names
+    return code[names[0]]
+
+
+@pytest.mark.parametrize("dv", [64, 128, 512])
+def test_merge_has_every_partial_in_flight(code, dv):
+    """A thread of the merge of up to 16 splits issues its 16 partial loads without a wait for memory in between."""
+    ins = _find(code, "12merge_kernel", f"ILi{dv}E")
+    loads = [i for i, x in enumerate(ins) if x.startswith("global_load_dwordx4")][-16:]
+    assert len(loads) == 16
+    waits = [x for x in ins[loads[0]:loads[-1]] if x.startswith("s_waitcnt") and "vmcnt" in x]
+    assert not waits, waits
