@@ -57,9 +57,11 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // wave, at most 256).  The token's request and page are uniform across the workgroup, so they are
 // looked up once, with scalar loads through the constant address space (the kernel never writes the
 // metadata).  A small wave is a chain of dependent loads (request, page, then the store), so it takes
-// one token per workgroup (launch_append), and the rows to be moved are loaded before the lookup: 128
-// tokens of 8 heads x 128 + 128 took 9 us as 16 workgroups of eight, about 5 us so (a 16-token-chunk layer
-// 181.4 -> 177.0 us).
+// one token per workgroup (launch_append), its request found by one candidate per lane and its row
+// loaded before that: 128 tokens of 8 heads x 128 + 128 took 9 us as 16 workgroups of eight, about 5 us so;
+// 2,048 of 32 heads 16.5 -> 11.6.  Eight tokens are moved in turn, each stored before the next is loaded, so
+// that the workgroups' reads and writes overlap: 8,192 tokens of 8 heads x 128 + 128 in 12.7 us, 5.3 TB/s, with
+// all eight loaded first 14.8; 65,536 of a latent cache 27.4, with that 33.2.
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ T const_load(const T* ptr) {
@@ -81,19 +83,17 @@ __global__ __launch_bounds__(256) void append_kernel(DevPlan p, const uint4* __r
     const int h = u / UC, c = u - h * UC;
     return c < KC ? k_new[(t * Hkv + h) * KC + c] : v_new[(t * Hkv + h) * VC + c - KC];
   };
-  uint4 first[TOK];
-#pragma unroll
-  for (int i = 0; i < TOK; ++i)
-    if (t0 + i < T && int(threadIdx.x) < per_tok) first[i] = load(t0 + i, threadIdx.x);
+  uint4 first;
+  if (TOK == 1 && int(threadIdx.x) < per_tok) first = load(t0, threadIdx.x);
   // request holding token t0: the last r with cu_r <= t0 (requests with no chunk share cu with the next).
-  // Bisection leaves at most 64 candidates, then every lane looks at one.
+  // For one token, bisection leaves at most 64 candidates, then every lane looks at one.
   int lo = 0, hi = p.num_requests - 1;
-  while (hi - lo >= 64) {
+  while (hi - lo >= (TOK == 1 ? 64 : 1)) {
     const int mid = (lo + hi + 1) >> 1;
     if (const_load(&p.reqs[mid].cu) <= t0) lo = mid; else hi = mid - 1;
   }
   int r = lo;
-  if (hi > lo) {
+  if (TOK == 1 && hi > lo) {
     const int mine = lo + int(threadIdx.x & 63);
     r = lo + __popcll(__ballot(mine <= hi && p.reqs[min(mine, hi)].cu <= t0)) - 1;
   }
@@ -109,11 +109,18 @@ __global__ __launch_bounds__(256) void append_kernel(DevPlan p, const uint4* __r
     for (int u = threadIdx.x; u < per_tok; u += blockDim.x) {
       const int h = u / UC;
       const int c = u - h * UC;
-      const uint4 x = u == int(threadIdx.x) ? first[i] : load(t, u);
-      if (c < KC)
-        k_pool[((page * Hkv + h) * B + slot) * KC + c] = x;
-      else
-        v_pool[((page * Hkv + h) * B + slot) * VC + c - KC] = x;
+      if constexpr (TOK == 1) {
+        const uint4 x = u == int(threadIdx.x) ? first : load(t, u);
+        if (c < KC)
+          k_pool[((page * Hkv + h) * B + slot) * KC + c] = x;
+        else
+          v_pool[((page * Hkv + h) * B + slot) * VC + c - KC] = x;
+      } else if (c < KC) {
+        k_pool[((page * Hkv + h) * B + slot) * KC + c] = k_new[(t * Hkv + h) * KC + c];
+      } else {
+        const int cv = c - KC;
+        v_pool[((page * Hkv + h) * B + slot) * VC + cv] = v_new[(t * Hkv + h) * VC + cv];
+      }
     }
   }
 }

@@ -47,3 +47,13 @@ def test_merge_has_every_partial_in_flight(code, dv):
     assert len(loads) == 16
     waits = [x for x in ins[loads[0]:loads[-1]] if x.startswith("s_waitcnt") and "vmcnt" in x]
     assert not waits, waits
+
+
+@pytest.mark.parametrize("dims", [(64, 64), (128, 128), (576, 0)])
+def test_append_of_many_tokens_moves_row_by_row(code, dims):
+    """The append of eight tokens a workgroup stores each token's row before it loads the next: with all rows
+    loaded first, the workgroups read together and then write together and keep half of the memory's
+    directions idle."""
+    ins = _find(code, "append_kernel", "ILi%dELi%dELi8E" % dims)
+    moves = [x.split("_")[1] for x in ins if re.match(r"global_(load|store)_dwordx4", x)]
+    assert moves.count("load") >= 8 and ("load", "load") not in zip(moves, moves[1:]), moves
