@@ -37,7 +37,8 @@ struct wavepp_plan {
   int32_t max_splits_used = 1;
   int32_t num_real_items = 0;
   std::vector<WorkItem> items;
-  std::vector<MergeItem> merges;
+  std::vector<MergeItem> merges;      // those that merge_wide_kernel takes first
+  int32_t num_merge_wide = 0, merge_rows = 0;
   int64_t partial_rows = 0;
   // metadata blob (uploaded as is) and its sub-array offsets
   std::vector<unsigned char> blob;
@@ -381,6 +382,42 @@ double grouped_cost(const wavepp_attn_shape& s, const wavepp_batch& b, int64_t t
          (part_mb > 0.0 ? f.merge_us : 0.0);
 }
 
+// Puts the merge items that take one row per workgroup (merge_wide_kernel) first and returns their number.  That
+// form cuts the chain of memory round trips of an item of many splits and pays a workgroup for every row.
+// Measured against merge_kernel on all items (attention with the merge, us):
+//  - items of more than 16 splits, alone: 87 splits, 16 to 1,024 rows of 128 lanes: 24-45 -> 12-36; 17 to 44
+//    splits, up to 1,024 rows: 1-6 less; 4,096 rows: 33 splits the same, 65 3 less; 16,384 rows: 17 splits 6-12
+//    more (64 lanes: 65,536 rows 182 -> 229), from 64 splits 7 less.  So up to 64 rows for every split (a
+//    workgroup of 512 lanes takes twice the threads: 32), and any number where each group of threads has 8
+//    splits to sum.
+//  - the other items of such a wave: sent through the same launch they cost about 1 us for 1,500 rows (16,384
+//    rows: 122 -> 132), a second launch 2-3 us, which the items of many splits make up from about 32 on.
+// The launch has as many workgroups for every item as the item of most rows (`most`) needs; one without a row
+// costs about a quarter of one with.
+int32_t merge_wide_items(std::vector<MergeItem>& merges, int most, int head_dim_v) {
+  int64_t rows = 0, parts = 0;           // rows and partial rows of the items of many splits
+  double cost = 0.0, rest = 0.0;         // their workgroups, and those of the others
+  for (const MergeItem& m : merges) {
+    const double workgroups = 0.75 * m.rows + 0.25 * most;
+    if (m.nsplit <= kMergeNarrow) {
+      rest += workgroups;
+    } else {
+      cost += workgroups;
+      rows += m.rows;
+      parts += int64_t(m.rows) * m.nsplit;
+    }
+  }
+  if (rows == 0) return 0;
+  const int threads = head_dim_v == 512 ? 512 : 256, groups = threads / (head_dim_v / 4);
+  const double splits = double(parts) / double(rows), width = threads / 256.0;
+  if (cost * width > 64.0 * splits && splits < 8.0 * groups) return 0;
+  if (rest * width <= 4096.0) return int32_t(merges.size());
+  if (splits < 32.0) return 0;
+  const auto end = std::stable_partition(merges.begin(), merges.end(),
+                                         [](const MergeItem& m) { return m.nsplit > kMergeNarrow; });
+  return int32_t(end - merges.begin());
+}
+
 }  // namespace
 
 namespace wavepp {
@@ -484,7 +521,8 @@ DevPlan make_dev(const wavepp_plan* plan, void* ws) {
   d.num_requests = plan->num_requests;
   d.num_items = int32_t(plan->items.size());
   d.num_merge = int32_t(plan->merges.size());
-  d.max_splits = plan->max_splits_used;
+  d.num_merge_wide = plan->num_merge_wide;
+  d.merge_rows = plan->merge_rows;
   d.total_tokens = plan->total_tokens;
   d.num_q_heads = plan->shape.num_q_heads;
   d.num_kv_heads = plan->shape.num_kv_heads;
@@ -749,6 +787,8 @@ int wavepp_attn_plan(const wavepp_attn_shape* shape, const wavepp_batch* batch, 
   plan->num_real_items = int32_t(items.size());
   plan->max_splits_used = max_used;
   plan->partial_rows = part_rows;
+  for (const MergeItem& m : plan->merges) plan->merge_rows = std::max(plan->merge_rows, m.rows);
+  plan->num_merge_wide = merge_wide_items(plan->merges, plan->merge_rows, s.head_dim_v);
   // workgroups per CU: the 4-wave grouped form runs two, or three at head dim 64; the others one
   const int per_cu = small_rows && !mla ? (s.head_dim_qk == 64 ? 3 : 2) : 1;
   plan->items = order_items(std::move(items), G, env_flag("WAVEPP_XCD_ORDER", true),

@@ -14,6 +14,7 @@ constexpr int kNumCu = 256;                // compute units of the chip: workgro
 constexpr int kNumXcd = 8;                 // L2 domains a launch is spread over, round-robin
 constexpr int kMlaRowsPerItem = 128;       // latent kernel: query rows per work item
 constexpr int kMlaKvTile = 64;             // latent kernel: keys per tile
+constexpr int kMergeNarrow = 16;           // merge: splits whose partials one thread loads at once
 
 // Header at the start of the uploaded metadata.
 struct alignas(16) MetaHeader {
@@ -74,7 +75,8 @@ struct DevPlan {
   int32_t num_q_heads, num_kv_heads, head_dim_qk, head_dim_v, page_size, kv_shared;
   int32_t rows_per_item;   // query rows per attention workgroup (32 per wave)
   float softmax_scale;
-  int32_t max_splits;      // most key-range splits of one item
+  int32_t num_merge_wide;  // leading merge items that take one row per workgroup (see merge_wide_items)
+  int32_t merge_rows;      // most rows of a merge item
 };
 
 // ---------------------------------------------------------------------------------------------

@@ -886,8 +886,6 @@ __global__ __launch_bounds__(256) void upload_kernel(const u32x4* __restrict__ s
 // deterministic.  A split that saw no key has lse = -inf and an all-zero partial row, which gets
 // weight 0.
 // ---------------------------------------------------------------------------------------------
-constexpr int kMergeNarrow = 16;   // most splits of an item that merge_kernel combines
-
 __device__ __forceinline__ float merge_weight(float l, float mx) {
   return l == -INFINITY ? 0.0f : fast_exp2((l - mx) * kLog2e);
 }
@@ -908,10 +906,10 @@ __device__ __forceinline__ void merge_store(const DevPlan& p, const MergeItem& m
   if (lse_out && c4 == 0) lse_out[orow] = mx + __logf(wsum);
 }
 
-// Up to kMergeNarrow splits an item: every LSE and partial of a (row, 4 value lanes) is loaded at once by
-// one thread (one memory round trip) and summed in split order.  Splits that the item does not have are left
-// undefined: a zero in their place once made the compiler wait for the first partial before it asked for the
-// others, 10-12 % of the kernel (128 value lanes, 21 requests in 5 splits: 49 us, 54 with that wait).
+// One thread per (row, 4 value lanes), summing in split order.  Up to kMergeNarrow splits, every LSE and partial is
+// loaded at once (one memory round trip); beyond that, two passes read four splits at a time.  Splits that the item
+// does not have are left undefined: a zero in their place once made the compiler wait for the first partial before
+// it asked for the others, 10-12 % of the kernel (128 value lanes, 21 requests in 5 splits: 49 us, 54 with that wait).
 template <int DV>
 __global__ __launch_bounds__(256) void merge_kernel(DevPlan p, __bf16* __restrict__ out, float* __restrict__ lse_out) {
   // workgroup (x = merge item, y = row group) handles RPB rows; one thread per (row, 4 value lanes)
@@ -929,6 +927,39 @@ __global__ __launch_bounds__(256) void merge_kernel(DevPlan p, __bf16* __restric
   float mx = -INFINITY;
   f32x4 acc = f32x4{};
   float wsum = 0.0f;
+  if (ns > kMergeNarrow) {
+    int s = 0;
+    for (; s + 4 <= ns; s += 4) {
+      float l[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) l[u] = lp[int64_t(s + u) * mi.rows];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) mx = fmaxf(mx, l[u]);
+    }
+    for (; s < ns; ++s) mx = fmaxf(mx, lp[int64_t(s) * mi.rows]);
+    for (s = 0; s + 4 <= ns; s += 4) {
+      float l[4];
+      f32x4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        l[u] = lp[int64_t(s + u) * mi.rows];
+        v[u] = *reinterpret_cast<const f32x4*>(op + (s + u) * ostep);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float w = merge_weight(l[u], mx);
+        acc += w * v[u];
+        wsum += w;
+      }
+    }
+    for (; s < ns; ++s) {
+      const float w = merge_weight(lp[int64_t(s) * mi.rows], mx);
+      acc += w * *reinterpret_cast<const f32x4*>(op + s * ostep);
+      wsum += w;
+    }
+    merge_store<DV>(p, mi, cu, lrow, c4, acc, wsum, mx, out, lse_out);
+    return;
+  }
   float l[kMergeNarrow];
   f32x4 v[kMergeNarrow];
 #pragma unroll
@@ -952,14 +983,14 @@ __global__ __launch_bounds__(256) void merge_kernel(DevPlan p, __bf16* __restric
   merge_store<DV>(p, mi, cu, lrow, c4, acc, wsum, mx, out, lse_out);
 }
 
-// Plans with an item of more splits (a few requests behind a long prefix: up to a piece per CU).  Such a wave has
-// few rows, and one thread that walks all splits of its row is a chain of memory round trips (four splits a trip,
-// once for the LSEs and once for the partials).  Here a workgroup takes one row: all its threads load the
-// LSEs for the maximum at once, then SG groups of threads each sum a run of neighbouring splits, eight loads in
-// flight, and the runs are added in order.
+// Items of more splits in few rows (a few requests behind a long prefix: up to a piece per CU; the host's
+// merge_wide_items says which).  One thread that walks all splits of its row is a chain of memory round trips (four
+// splits a trip, once for the LSEs and once for the partials).  Here a workgroup takes one row: all its threads load
+// the LSEs for the maximum at once, then SG groups of threads each sum a run of neighbouring splits, eight loads in
+// flight, and the runs are added in order.  Items of few splits may come along in the same launch.
 // Attention with the merge, this form against one thread a row: latent, 16 heads, 4 tokens behind 131,072, 228 splits
-// 87 -> 57 us; 16/1 heads of 128, 121 splits 49 -> 32 us; 8/2 of 64, 92 splits 39 -> 26 us; 64/8 of 128, 63
-// splits 120 -> 112 us; the same within 1 % at 17 to 40 splits.  Up to 16, a thread has every load in flight anyway.
+// 87 -> 57 us; 16/1 heads of 128, 121 splits 49 -> 32 us; 8/2 of 64, 92 splits 39 -> 26 us.  Up to 16, a thread has
+// every load in flight anyway.
 template <int DV>
 __global__ __launch_bounds__(DV == 512 ? 512 : 256) void merge_wide_kernel(DevPlan p, __bf16* __restrict__ out,
                                                                            float* __restrict__ lse_out) {
@@ -1105,12 +1136,16 @@ hipError_t launch_merge(const DevPlan& p, void* out, float* lse, hipStream_t str
   auto oo = static_cast<__bf16*>(out);
   const int dv = p.head_dim_v;
   if (dv != 64 && dv != 128 && dv != 512) return hipErrorInvalidValue;
-  const bool wide = p.max_splits > kMergeNarrow;
-  const int rpb = wide ? 1 : 256 / (dv / 4);
-  const dim3 grid(p.num_merge, (p.rows_per_item + rpb - 1) / rpb), block(wide && dv == 512 ? 512 : 256);
-#define WAVEPP_MERGE(DV_)                                                                      \
-  if (wide) hipLaunchKernelGGL((merge_wide_kernel<DV_>), grid, block, 0, stream, p, oo, lse); \
-  else hipLaunchKernelGGL((merge_kernel<DV_>), grid, block, 0, stream, p, oo, lse);
+  // the first num_merge_wide items one row per workgroup, the others by one thread per (row, 4 value lanes)
+  DevPlan narrow = p;
+  narrow.merges += p.num_merge_wide;
+  narrow.num_merge -= p.num_merge_wide;
+  const int rpb = 256 / (dv / 4);
+  const dim3 wide_grid(p.num_merge_wide, p.merge_rows), wide_block(dv == 512 ? 512 : 256);
+  const dim3 grid(narrow.num_merge, (p.merge_rows + rpb - 1) / rpb), block(256);
+#define WAVEPP_MERGE(DV_)                                                                                         \
+  if (p.num_merge_wide) hipLaunchKernelGGL((merge_wide_kernel<DV_>), wide_grid, wide_block, 0, stream, p, oo, lse); \
+  if (narrow.num_merge) hipLaunchKernelGGL((merge_kernel<DV_>), grid, block, 0, stream, narrow, oo, lse);
   if (dv == 128) {
     WAVEPP_MERGE(128)
   } else if (dv == 64) {

@@ -1,6 +1,7 @@
-"""GPU merge of many key-range splits against the oracle: items of more than 16 splits take one row per
-workgroup, with runs of neighbouring splits summed by groups of threads; split counts that leave the last
-groups without a split, rows that do not fill an item, and items of few splits in the same launch."""
+"""GPU merge of many key-range splits against the oracle: items of more than 16 splits in few rows take one row
+per workgroup, with runs of neighbouring splits summed by groups of threads; split counts that leave the last
+groups without a split, rows that do not fill an item, and items of few splits in the same launch or, when they
+have many rows, in one of their own; items of many splits and many rows are walked by a thread a row."""
 import pytest
 
 import paper_2609_35263_amd as wp
@@ -18,6 +19,9 @@ pytestmark = pytest.mark.gpu
     ((64, 8, 128, 128), [11480], [40], 90),            # 8-wave items
     ((16, 1, 576, 512), [1085], [3], 17),              # latent: 4 groups
     ((128, 1, 576, 512), [8958, 50], [2, 1], 140),
+    ((64, 8, 128, 128), [6000, 300], [2, 70], 47),     # 128 rows of 47 splits, 4,480 of 3: a launch each
+    ((16, 1, 64, 64), [2560], [90], 21),               # 1,440 rows of 21 splits: a thread a row, splits by fours
+    ((16, 1, 576, 512), [1100, 500], [40, 3], 18),     # the same, latent, with an item of few splits
 ])
 def test_many_splits(shape, prefix, chunk, splits):
     import torch

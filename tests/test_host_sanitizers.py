@@ -7,7 +7,8 @@ launchers, and driven by seeded randomized inputs:
 * address + undefined-behaviour sanitizers over ``tests/native/host_fuzz.cpp`` (every accepted
   attention plan's work list is checked for exact coverage; every status against a restatement of
   the validation rules);
-* the same over ``tests/native/kda_chains.cpp`` (a KDA plan's chains, walked as the kernel's workgroups do);
+* the same over ``tests/native/kda_chains.cpp`` (a KDA plan's chains, walked as the kernel's workgroups do) and
+  ``tests/native/merge_items.cpp`` (the form of the merge that a plan's items take);
 * thread sanitizer over ``tests/native/hints_threads.cpp`` (concurrent add / detach / probe of the
   sharded hint index).
 
@@ -60,13 +61,15 @@ def test_host_code_under_address_and_undefined_behaviour_sanitizers():
             assert "host_fuzz ok" in out
 
 
-def test_kda_chains_run_once_and_evenly():
+@pytest.mark.parametrize("source,name", [("kda_host.cpp", "kda_chains"), ("host.cpp", "merge_items")])
+def test_plans_of_the_kernels_work(source, name):
+    """The KDA chains of each workgroup and the merge form of each item, as the kernels find them in a plan."""
     with tempfile.TemporaryDirectory() as d:
-        exe = os.path.join(d, "kda_chains")
-        others = [f for f in HOST_SOURCES if not f.endswith("kda_host.cpp")]     # the test includes that one
-        _build(exe, others + [os.path.join(NATIVE, "launch_stubs.cpp"), os.path.join(NATIVE, "kda_chains.cpp")],
+        exe = os.path.join(d, name)
+        others = [f for f in HOST_SOURCES if os.path.basename(f) != source]     # the test includes that one
+        _build(exe, others + [os.path.join(NATIVE, "launch_stubs.cpp"), os.path.join(NATIVE, name + ".cpp")],
                "address,undefined")
-        assert "kda_chains ok" in _run(exe, [], {"ASAN_OPTIONS": "detect_leaks=1"})
+        assert f"{name} ok" in _run(exe, [], {"ASAN_OPTIONS": "detect_leaks=1"})
 
 
 def test_hint_index_under_thread_sanitizer():
