@@ -137,6 +137,14 @@ double item_cost(const WorkItem& it, int G) {
 class SlotClock {
  public:
   explicit SlotClock(int slots) : busy_(size_t(std::max(1, slots)), 0.0) {}
+  // the longest-first items of `times`, in order, on empty slots, until a slot's time reaches `limit`
+  SlotClock(int slots, const std::vector<double>& times, double limit = INFINITY) : SlotClock(slots) {
+    // the first go to a slot each; ascending, they are a heap already
+    const size_t n = std::min(times.size(), busy_.size());
+    std::reverse_copy(times.begin(), times.begin() + n, busy_.end() - n);
+    if (n) longest_ = times[0];
+    for (size_t i = n; i < times.size() && longest_ < limit; ++i) add(times[i]);
+  }
   // the next item of `time` goes to the slot that is free first
   void add(double time) {
     const double t = busy_[0] + time;
@@ -158,6 +166,44 @@ class SlotClock {
   double longest_ = 0.0;
 };
 
+// Sorts `order` by `key` (key[i] belongs to order[i]), largest first, equal keys in their order: a radix sort over
+// the bytes in which the keys differ.  Some thousand items take a quarter of the time of a comparison sort,
+// which mispredicts half its branches.
+void sort_descending(std::vector<uint64_t>& key, std::vector<uint32_t>& order) {
+  const size_t n = key.size();
+  if (n <= 48) {                       // too few to pay for the buckets
+    for (size_t i = 1; i < n; ++i) {
+      const uint64_t k = key[i];
+      const uint32_t o = order[i];
+      size_t j = i;
+      for (; j > 0 && key[j - 1] < k; --j) {
+        key[j] = key[j - 1];
+        order[j] = order[j - 1];
+      }
+      key[j] = k;
+      order[j] = o;
+    }
+    return;
+  }
+  uint64_t differ = 0;
+  for (uint64_t k : key) differ |= k ^ key[0];
+  std::vector<uint64_t> key_to(n);
+  std::vector<uint32_t> order_to(n);
+  for (int shift = 0; shift < 64; shift += 8) {
+    if (((differ >> shift) & 255) == 0) continue;
+    uint32_t at[257] = {};
+    for (uint64_t k : key) ++at[256 - ((k >> shift) & 255)];         // the bucket after the key's own
+    for (int b = 0; b < 256; ++b) at[b + 1] += at[b];
+    for (size_t i = 0; i < n; ++i) {
+      const uint32_t to = at[255 - ((key[i] >> shift) & 255)]++;
+      key_to[to] = key[i];
+      order_to[to] = order[i];
+    }
+    key.swap(key_to);
+    order.swap(order_to);
+  }
+}
+
 // Order items heaviest first and spread them over the L2 domains: consecutive workgroup ids go
 // round-robin to the kNumXcd domains, so item index k*kNumXcd + x runs on domain x.  Items of one
 // (request, KV head), a stream, read the same K/V pages; keeping them on one domain lets its L2 serve the
@@ -169,15 +215,22 @@ class SlotClock {
 std::vector<WorkItem> order_items(std::vector<WorkItem> items, int G, bool xcd_aware, bool stream_major, int slots,
                                   int kv_tile, double overhead) {
   const size_t n = items.size();
-  typedef std::pair<double, uint32_t> Key;   // (size, index): largest first, in index order where equal
-  auto larger = [](const Key& a, const Key& b) { return a.first > b.first || (a.first == b.first && a.second < b.second); };
-  std::vector<Key> by_cost(n);
-  for (size_t i = 0; i < n; ++i) by_cost[i] = Key(item_cost(items[i], G), uint32_t(i));
+  typedef std::pair<double, uint32_t> Key;   // (size, index)
+  std::vector<double> cost(n);
+  std::vector<uint32_t> by_cost(n);          // items, largest cost first, in index order where equal
+  {
+    std::vector<uint64_t> key(n);
+    for (size_t i = 0; i < n; ++i) {
+      cost[i] = item_cost(items[i], G);
+      memcpy(&key[i], &cost[i], sizeof(double));          // positive doubles sort like their bits
+      by_cost[i] = uint32_t(i);
+    }
+    sort_descending(key, by_cost);
+  }
   if (!xcd_aware || n <= 1) {
-    std::sort(by_cost.begin(), by_cost.end(), larger);
     std::vector<WorkItem> out;
     out.reserve(n);
-    for (const Key& k : by_cost) out.push_back(items[k.second]);
+    for (uint32_t i : by_cost) out.push_back(items[i]);
     return out;
   }
   std::vector<uint32_t> stream(n), first;      // stream of an item, first item of a stream
@@ -189,48 +242,47 @@ std::vector<WorkItem> order_items(std::vector<WorkItem> items, int G, bool xcd_a
       first.push_back(uint32_t(i));
     }
     stream[i] = uint32_t(first.size() - 1);
-    by_stream_cost.back().first += by_cost[i].first;
-    total += by_cost[i].first;
+    by_stream_cost.back().first += cost[i];
+    total += cost[i];
     biggest = std::max(biggest, by_stream_cost.back().first);
   }
   // Time goes by tiles, not rows: an item's workgroup runs its key tiles in the same time however few of its
   // rows are used.
-  std::vector<double> time(n);
+  std::vector<uint64_t> tiles(n);
   double time_sum = 0.0, time_max = 0.0;
   for (size_t i = 0; i < n; ++i) {
-    time[i] = double(ceil_div(items[i].kv_end - items[i].kv_begin, kv_tile)) + overhead;
-    time_sum += time[i];
-    time_max = std::max(time_max, time[i]);
+    tiles[i] = uint64_t(uint32_t(items[i].kv_end - items[i].kv_begin + kv_tile - 1) / uint32_t(kv_tile));
+    time_sum += double(tiles[i]) + overhead;
+    time_max = std::max(time_max, double(tiles[i]) + overhead);
   }
   typedef std::vector<std::vector<uint32_t>> Lists;
   // Individual placement: longest first, each to the least loaded domain.  Items of equal time go by cost, that
   // is by their exact key count: a few requests of the same lengths then come in turn and land on a domain
   // each, whose L2 serves their re-reads (8 requests of 131,072 cached tokens on the latent form: 97 % of
   // the reads, against 87 % when each request's equal items are dealt out over all domains).
-  std::vector<double> cost(n);
-  for (size_t i = 0; i < n; ++i) cost[i] = by_cost[i].first;
   auto place_items = [&] {
-    std::vector<Key> by_time(n);
-    for (size_t i = 0; i < n; ++i) by_time[i] = Key(time[i], uint32_t(i));
-    std::sort(by_time.begin(), by_time.end(), [&](const Key& a, const Key& b) {
-      if (a.first != b.first) return a.first > b.first;
-      if (cost[a.second] != cost[b.second]) return cost[a.second] > cost[b.second];
-      return a.second < b.second;
-    });
+    std::vector<uint64_t> key(n);
+    std::vector<uint32_t> by_time(by_cost);
+    for (size_t i = 0; i < n; ++i) key[i] = tiles[by_cost[i]];
+    sort_descending(key, by_time);
     Lists out(kNumXcd);
-    double busy[kNumXcd] = {};
-    for (const Key& k : by_time) {
-      const int x = int(std::min_element(busy, busy + kNumXcd) - busy);
-      out[x].push_back(k.second);
-      busy[x] += k.first;
+    for (auto& l : out) l.reserve(2 * n / kNumXcd);
+    Key busy[kNumXcd];                       // least loaded first, in index order where equal
+    for (int x = 0; x < kNumXcd; ++x) busy[x] = Key(0.0, uint32_t(x));
+    for (uint32_t i : by_time) {
+      out[busy[0].second].push_back(i);
+      const Key k(busy[0].first + (double(tiles[i]) + overhead), busy[0].second);
+      int x = 0;
+      for (; x + 1 < kNumXcd && busy[x + 1] < k; ++x) busy[x] = busy[x + 1];
+      busy[x] = k;
     }
     return out;
   };
   Lists lists;
   if (first.size() >= size_t(2 * kNumXcd) && biggest <= 0.5 * total / kNumXcd) {
     lists.resize(kNumXcd);
-    std::sort(by_cost.begin(), by_cost.end(), larger);
-    std::sort(by_stream_cost.begin(), by_stream_cost.end(), larger);
+    std::sort(by_stream_cost.begin(), by_stream_cost.end(),
+              [](const Key& a, const Key& b) { return a.first > b.first || (a.first == b.first && a.second < b.second); });
     std::vector<int> where(first.size(), 0);
     double load[kNumXcd] = {};
     for (const Key& k : by_stream_cost) {
@@ -243,13 +295,13 @@ std::vector<WorkItem> order_items(std::vector<WorkItem> items, int G, bool xcd_a
       // first: the items running together on the domain's CUs then mostly belong to one stream and
       // read its tiles at about the same time, so the domain's L2 serves the re-reads
       std::vector<uint32_t> at(first), sorted(n);
-      for (const Key& k : by_cost) sorted[at[stream[k.second]]++] = k.second;
+      for (uint32_t i : by_cost) sorted[at[stream[i]]++] = i;
       for (const Key& k : by_stream_cost) {
         const size_t end = k.second + 1 < first.size() ? first[k.second + 1] : n;
         lists[where[k.second]].insert(lists[where[k.second]].end(), sorted.begin() + first[k.second], sorted.begin() + end);
       }
     } else {
-      for (const Key& k : by_cost) lists[where[stream[k.second]]].push_back(k.second);
+      for (uint32_t i : by_cost) lists[where[stream[i]]].push_back(i);
     }
     // With few items per slot, the last stream of a domain can run on a few of its slots alone.  Both orders
     // are played through (each domain hands its list to its slots in order); the streams stay together
@@ -257,19 +309,22 @@ std::vector<WorkItem> order_items(std::vector<WorkItem> items, int G, bool xcd_a
     // 12 requests of 0.1-6 K cached and 37-1,500 new tokens, 24/4 heads: 125 tiles against 102, 331 us
     // against 281.
     if (n <= size_t(16) * slots) {
-      auto makespan = [&](const Lists& ls) {
+      // the longest domain's time, or the first that is not below `limit`
+      auto makespan = [&](const Lists& ls, double limit) {
         double longest = 0.0;
         for (const auto& l : ls) {
           SlotClock clock(slots / kNumXcd);
-          for (uint32_t i : l) clock.add(time[i]);
-          longest = std::max(longest, clock.longest());
+          for (size_t i = 0; i < l.size() && longest < limit; ++i) {
+            clock.add(double(tiles[l[i]]) + overhead);
+            longest = std::max(longest, clock.longest());
+          }
         }
         return longest;
       };
-      const double together = makespan(lists);
+      const double together = makespan(lists, INFINITY);
       if (std::max(time_max, time_sum / slots) < 0.95 * together) {   // no order is shorter than that
         Lists single = place_items();
-        if (makespan(single) < 0.95 * together) lists = std::move(single);
+        if (makespan(single, 0.95 * together) < 0.95 * together) lists = std::move(single);
       }
     }
   } else {
@@ -300,23 +355,32 @@ struct SplitPlan {
 // played through.
 double split_cost(const std::vector<int64_t>& ntiles, const SplitPlan& sp, int slots, double overhead, double merge,
                   double best) {
-  std::vector<int64_t> len;
-  len.reserve(size_t(sp.pieces));
+  std::vector<uint64_t> len;                 // equal pieces of an item, and its remainder
+  std::vector<uint32_t> number;
+  len.reserve(2 * ntiles.size());
+  number.reserve(2 * ntiles.size());
   double partials = 0.0, sum = 0.0;
-  int64_t most = 0;
+  int64_t count = 0;
+  uint32_t most = 0;
   for (size_t i = 0; i < ntiles.size(); ++i) {
-    const int64_t n = ntiles[i], t = sp.tps[i];
-    for (int64_t k = 0; k < n; k += t) len.push_back(std::min(t, n - k));
-    if (n > t) partials += double(ceil_div(n, t));
+    const uint32_t n = uint32_t(ntiles[i]), t = uint32_t(sp.tps[i]), whole = n / t, left = n - whole * t;
+    if (whole) len.push_back(t), number.push_back(whole);
+    if (left) len.push_back(left), number.push_back(1);
+    const uint32_t k = whole + (left != 0);
+    if (k > 1) partials += double(k);
+    count += k;
     sum += double(n);
-    most = std::max(most, std::min(n, t));
+    most = std::max(most, whole ? t : left);
   }
-  const double bound = std::max(double(most) + overhead, (sum + overhead * double(len.size())) / slots) + merge * partials;
+  const double bound = std::max(double(most) + overhead, (sum + overhead * double(count)) / slots) + merge * partials;
   if (bound >= best) return bound;
-  std::sort(len.begin(), len.end(), std::greater<int64_t>());
-  SlotClock clock(slots);
-  for (int64_t n : len) clock.add(double(n) + overhead);
-  return clock.longest() + merge * partials;
+  if (count <= slots) return double(most) + overhead + merge * partials;
+  sort_descending(len, number);
+  std::vector<double> times;
+  times.reserve(size_t(count));
+  for (size_t i = 0; i < len.size(); ++i) times.insert(times.end(), number[i], double(len[i]) + overhead);
+  const double limit = best - merge * partials, longest = SlotClock(slots, times, limit).longest();
+  return longest < limit ? longest + merge * partials : std::max(best, longest + merge * partials);
 }
 
 // Modelled time of a small grouped wave in the 8-wave form (attention and merge, microseconds), its key
@@ -375,10 +439,9 @@ double grouped_cost(const wavepp_attn_shape& s, const wavepp_batch& b, int64_t t
     pieces.push_back({double(g.tiles - tps * (S - 1)) * w + f.overhead, g.count});
   }
   std::sort(pieces.begin(), pieces.end(), std::greater<std::pair<double, int64_t>>());
-  SlotClock clock(f.slots);
-  for (const auto& x : pieces)
-    for (int64_t i = 0; i < x.second; ++i) clock.add(x.first);
-  return std::max(f.tile_us * clock.longest() + f.base_us, 0.19 * kv_mb) + f.part_us_per_mb * part_mb +
+  std::vector<double> times;
+  for (const auto& x : pieces) times.insert(times.end(), size_t(x.second), x.first);
+  return std::max(f.tile_us * SlotClock(f.slots, times).longest() + f.base_us, 0.19 * kv_mb) + f.part_us_per_mb * part_mb +
          (part_mb > 0.0 ? f.merge_us : 0.0);
 }
 
@@ -681,8 +744,8 @@ int wavepp_attn_plan(const wavepp_attn_shape* shape, const wavepp_batch* batch, 
   if (max_splits >= 1) {
     for (size_t i = 0; i < base.size(); ++i) split.tps[i] = ceil_div(ntiles[i], std::min<int64_t>(max_splits, ntiles[i]));
   } else if (int64_t(base.size()) < fill_target) {
-    auto auto_splits = [&](int64_t n, int64_t T) {
-      return std::max<int64_t>(1, std::min<int64_t>(ceil_div(n, T), n / min_split_tiles));
+    auto auto_splits = [&](int64_t n, int64_t T) {       // (32-bit divisions: this runs a dozen times an item)
+      return std::max<int64_t>(1, std::min(uint32_t(n + T - 1) / uint32_t(T), uint32_t(n) / uint32_t(min_split_tiles)));
     };
     const int64_t longest = base.empty() ? 1 : *std::max_element(ntiles.begin(), ntiles.end());
     // even splits of at most `target` items: the smallest T (no shorter than the minimum) that keeps to it;
@@ -702,9 +765,11 @@ int wavepp_attn_plan(const wavepp_attn_shape* shape, const wavepp_batch* batch, 
         lo = hi;
       }
       SplitPlan sp;
+      sp.tps.reserve(ntiles.size());
       for (int64_t t : ntiles) {
-        sp.tps.push_back(ceil_div(t, auto_splits(t, lo)));
-        sp.pieces += ceil_div(t, sp.tps.back());
+        const uint32_t n = uint32_t(t), splits = uint32_t(auto_splits(t, lo)), tps = (n + splits - 1) / splits;
+        sp.tps.push_back(tps);
+        sp.pieces += (n + tps - 1) / tps;
       }
       return sp;
     };
@@ -737,15 +802,24 @@ int wavepp_attn_plan(const wavepp_attn_shape* shape, const wavepp_batch* batch, 
       };
       if (int64_t(base.size()) < slots) consider(even(slots));
       const int64_t sum = std::accumulate(ntiles.begin(), ntiles.end(), int64_t(0));
+      int64_t last = 0;
       for (double f : {1.0, 1.04, 1.08, 1.15, 1.25}) {
         const int64_t T = std::max<int64_t>(min_split_tiles, int64_t(std::ceil(f * double(sum) / slots)));
+        if (T == last) continue;
+        last = T;
         SplitPlan sp;
-        for (int64_t n : ntiles) {
-          int64_t t = std::min(T, n);
+        sp.tps.reserve(ntiles.size());
+        for (int64_t tiles : ntiles) {
+          const uint32_t n = uint32_t(tiles);
+          uint32_t t = std::min(uint32_t(T), n), whole = n / t, left = n - whole * t;
           // a remainder below the minimum split length is shared out over the whole pieces
-          if (n % t && n % t < min_split_tiles) t = ceil_div(n, n / t);
+          if (left && left < min_split_tiles) {
+            t = (n + whole - 1) / whole;
+            whole = n / t;
+            left = n - whole * t;
+          }
           sp.tps.push_back(t);
-          sp.pieces += ceil_div(n, t);
+          sp.pieces += whole + (left != 0);
         }
         consider(std::move(sp));
       }

@@ -511,3 +511,25 @@ def test_grouped_splits_one_or_two_rounds(prefix, chunk, once, monkeypatch):
     for r in real:
         last[tuple(r[:3])] = max(last.get(tuple(r[:3]), 0), int(r[7]))
     assert all(r[5] - r[4] >= 1024 for r in real if r[7] < last[tuple(r[:3])])
+
+
+def test_planning_takes_less_than_a_sort():
+    """A wave for which both placements of its items are played through is planned in 0.6 of the time that a stable
+    sort of twice as many numbers takes (1.8 with comparison sorts through an index)."""
+    import time
+    rng = np.random.default_rng(9)
+    spec = wl.custom_wave(64, 8, 128, 128, 64, rng.integers(400, 500, 18), rng.integers(400, 500, 18), seed=2)
+    n = wp.plan_for(spec).info()["num_real_items"]
+    assert n > 1000
+    x = np.random.default_rng(1).random(2 * n)
+
+    def best(f):
+        took = []
+        for _ in range(40):
+            start = time.perf_counter()
+            f()
+            took.append(time.perf_counter() - start)
+        return min(took)
+
+    plan, sort = best(lambda: wp.plan_for(spec)), best(lambda: np.argsort(x, kind="stable"))
+    assert plan < 1.1 * sort, (plan, sort)
