@@ -194,3 +194,24 @@ def test_kda_correlated_keys(extreme):
     if extreme:
         t["alpha"][70:90, :, :40] = 0.0
     _check_custom(spec, t, "correlated keys")
+
+
+@pytest.mark.parametrize("heads,lens", [
+    (43, [70, 66, 5, 130, 3, 64, 90]),          # 301 chains of one to three blocks, listed
+    (53, [60, 33, 64, 7, 50]),                  # 265 chains of one block, in the fixed order
+])
+def test_kda_slow_channels_where_chains_meet(heads, lens):
+    """Zero decays in 20 channels (two passes of the exact path) of the last block of every other request and in
+    40 (three) of the first block of every third: the passes, and with them the barriers of both halves of the
+    workgroup, change from one chain to the next and stand between a snapshot's store and the next one's load."""
+    R = len(lens)
+    spec = wk.custom(heads, 128, 128, lens, [i if i % 3 else -1 for i in range(R)], [R + i for i in range(R)], 2 * R)
+    t = wk.make_tensors(spec, seed=140 + heads)
+    cu = spec.cu_tokens
+    for r, n in enumerate(lens):
+        if r % 2 == 0:
+            last = (n - 1) // 64 * 64
+            t["alpha"][cu[r] + last:cu[r] + n, :, 5:25] = 0.0
+        if r % 3 == 0:
+            t["alpha"][cu[r]:cu[r] + min(n, 64), :, 30:70] = 0.0
+    _check_custom(spec, t, f"slow channels, {heads} heads")
