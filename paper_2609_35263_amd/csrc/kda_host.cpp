@@ -46,38 +46,62 @@ int check_ws(const wavepp_kda_plan_t* plan, void* ws, size_t ws_bytes) {
 // short ones: 1 x 4,096 and 63 x 512 tokens, 32 heads: 120 blocks on the busiest workgroup, 600 us, against 72
 // and 438-448; 1 x 8,192 and 255 x 512, 16 heads: 1,220 us against 830-850.  A chain costs its blocks and about
 // half a block for its snapshots (16 chains of 4 blocks a workgroup take 411 us, one of 64 blocks 369).
-// Empty where the fixed order is as good: at most one chain a workgroup, or all of the same number of blocks (64
-// requests of one token, 64 heads: 114 us in the fixed order, 133 listed); and beyond kKdaMaxListed chains,
-// thousands a workgroup, where its imbalance is small but for a chain as long as many.  Listing takes about 5 ns
-// a chain.
+// Empty where the fixed order is as good: at most one chain a workgroup, all of the same number of blocks, or less
+// than 2 % between the two (64 requests of 200-312 tokens, 64 heads: 442 us in the fixed order, 444-446 listed);
+// and beyond kKdaMaxListed chains, thousands a workgroup, where its imbalance is small but for a chain as long as
+// many.  Listing takes about 5 ns a chain.
 // The chains of `items` (longest first) come in runs of equal length.  Within a run the workgroups' new loads
-// only grow, so the least loaded one is at the head of one of two sorted queues: no heap.
+// only grow, so the least loaded one is at the head of one of two sorted queues: no heap.  Of equally loaded ones the
+// last that was given a chain is first, so that rounds of equal chains alternate in direction like the fixed order (64
+// requests of one token, 64 heads: 114 us in the fixed order, 116 listed so, 133 first given first).
 std::vector<int32_t> chain_owners(const std::vector<KdaItem>& items, int heads) {
   std::vector<int32_t> owner;
   auto blocks = [&](size_t i) { return int64_t(items[i].len + kKdaBlock - 1) / kKdaBlock; };
+  auto cost_of = [&](size_t i) { return 2 * blocks(i) + 1; };         // of a chain of item i, in half blocks
   const int64_t chains = int64_t(items.size()) * heads;
   if (chains <= kNumCu || chains > kKdaMaxListed || blocks(0) == blocks(items.size() - 1)) return owner;
+  // the busiest workgroup in the fixed order, against the least that any order can give it
+  int64_t fixed[kNumCu] = {}, total = 0, n = 0;
+  for (size_t i = 0; i < items.size(); ++i) {
+    const int64_t cost = cost_of(i);
+    for (int h = 0; h < heads; ++h, ++n) fixed[n / kNumCu & 1 ? kNumCu - 1 - n % kNumCu : n % kNumCu] += cost;
+    total += cost * heads;
+  }
+  const int64_t busiest = *std::max_element(fixed, fixed + kNumCu);
+  if (50 * busiest <= 51 * std::max(total / kNumCu, cost_of(0))) return owner;
   owner.resize(size_t(chains));
   typedef std::pair<int64_t, int32_t> Load;           // (work, workgroup)
   std::vector<Load> ready, given, rest;
-  given.reserve(size_t(chains));
+  given.reserve(size_t(chains));           // (no reallocation while it is read and added to)
   for (int32_t w = 0; w < kNumCu; ++w) ready.push_back(Load(0, w));
   int64_t c = 0;
   for (size_t i = 0, j; i < items.size(); i = j) {
     for (j = i + 1; j < items.size() && blocks(j) == blocks(i);) ++j;
-    const int64_t cost = 2 * blocks(i) + 1, end = int64_t(j) * heads;
+    const int64_t cost = cost_of(i), end = int64_t(j) * heads;
     size_t r = 0, g = 0;
     given.clear();
-    for (; c < end; ++c) {
+    while (c < end) {
       const bool old = r < ready.size() && (g == given.size() || ready[r].first <= given[g].first);
-      const Load least = old ? ready[r++] : given[g++];
-      owner[size_t(c)] = least.second;
-      given.push_back(Load(least.first + cost, least.second));
+      std::vector<Load>& from = old ? ready : given;
+      size_t& head = old ? r : g;
+      const int64_t load = from[head].first;
+      size_t tail = head;
+      while (tail < from.size() && from[tail].first == load) ++tail;
+      size_t left = tail;
+      for (; left > head && c < end; ++c) {
+        const int32_t w = from[--left].second;
+        owner[size_t(c)] = w;
+        given.push_back(Load(load + cost, w));
+      }
+      // what is left of the equal ones (at the run's end) moves up to the others
+      std::move_backward(from.begin() + head, from.begin() + left, from.begin() + tail);
+      head = tail - (left - head);
     }
     rest.clear();
     std::merge(ready.begin() + r, ready.end(), given.begin() + g, given.end(), std::back_inserter(rest));
     ready.swap(rest);
   }
+  if (50 * busiest <= 51 * ready.back().first) owner.clear();
   return owner;
 }
 

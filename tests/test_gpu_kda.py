@@ -164,18 +164,26 @@ def test_kda_many_heads():
     _check_custom(spec, wk.make_tensors(spec, seed=112), "96 heads")
 
 
-@pytest.mark.parametrize("heads,lens", [
-    (1, [1]),                                   # one workgroup, one block
-    (43, [64, 128, 1, 65, 200, 63]),            # 258 chains: two workgroups take a second one
-    (96, [130, 70, 64, 33, 5, 1, 192]),         # 672 chains of unlike lengths, by load
-    (43, [64, 60, 1] * 5),      # 645 chains of one block each: fixed order, a part of the third round
-    (8, [700] + [70, 5] * 20),                  # long chains alone on their workgroups, the others share the short ones
+def _listed(spec):
+    """Whether the plan lists each workgroup's chains after the items (of 32 bytes, after a header of 16)."""
+    info = wp.kda_plan_for(spec).info()
+    return info["metadata_bytes"] > 16 + 32 * info["num_items"]
+
+
+@pytest.mark.parametrize("heads,lens,listed", [
+    (1, [1], False),                                   # one workgroup, one block
+    (43, [64, 128, 1, 65, 200, 63], False),            # 258 chains: two workgroups take a second one, in reverse order
+    (96, [130, 70, 64, 33, 5, 1, 192], False),         # 672 chains, a part of the third round
+    (43, [64, 60, 1] * 5, False),                      # 645 chains of one block each
+    (8, [400] + [70, 5] * 40, True),                   # 8 long chains alone on their workgroups, 640 short ones shared out
+    (1, [1000, 640] + [65, 3] * 300, True),            # the same with one head: item and chain numbers agree
 ])
-def test_kda_chains_per_workgroup(heads, lens):
-    """More chains than resident workgroups, of one to four blocks: every chain starts from its own snapshot
-    (or none) and leaves its own, whatever its workgroup ran before."""
+def test_kda_chains_per_workgroup(heads, lens, listed):
+    """More chains than resident workgroups, of one to sixteen blocks, in the fixed order and by load: every chain
+    starts from its own snapshot (or none) and leaves its own, whatever its workgroup ran before."""
     R = len(lens)
     spec = wk.custom(heads, 128, 128, lens, [i if i % 3 else -1 for i in range(R)], [R + i for i in range(R)], 2 * R)
+    assert _listed(spec) == listed
     _check_custom(spec, wk.make_tensors(spec, seed=120 + heads), f"{heads} heads, {R} requests")
 
 
@@ -196,16 +204,18 @@ def test_kda_correlated_keys(extreme):
     _check_custom(spec, t, "correlated keys")
 
 
-@pytest.mark.parametrize("heads,lens", [
-    (43, [70, 66, 5, 130, 3, 64, 90]),          # 301 chains of one to three blocks, listed
-    (53, [60, 33, 64, 7, 50]),                  # 265 chains of one block, in the fixed order
+@pytest.mark.parametrize("heads,lens,listed", [
+    (43, [70, 66, 5, 130, 3, 64, 90], False),      # 301 chains of one to three blocks
+    (53, [60, 33, 64, 7, 50], False),              # 265 chains of one block
+    (43, [330, 66, 5, 3, 64, 90, 1, 60, 30, 10, 7, 33, 64], True),
 ])
-def test_kda_slow_channels_where_chains_meet(heads, lens):
+def test_kda_slow_channels_where_chains_meet(heads, lens, listed):
     """Zero decays in 20 channels (two passes of the exact path) of the last block of every other request and in
     40 (three) of the first block of every third: the passes, and with them the barriers of both halves of the
     workgroup, change from one chain to the next and stand between a snapshot's store and the next one's load."""
     R = len(lens)
     spec = wk.custom(heads, 128, 128, lens, [i if i % 3 else -1 for i in range(R)], [R + i for i in range(R)], 2 * R)
+    assert _listed(spec) == listed
     t = wk.make_tensors(spec, seed=140 + heads)
     cu = spec.cu_tokens
     for r, n in enumerate(lens):
