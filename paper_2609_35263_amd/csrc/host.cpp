@@ -137,13 +137,13 @@ double item_cost(const WorkItem& it, int G) {
 class SlotClock {
  public:
   explicit SlotClock(int slots) : busy_(size_t(std::max(1, slots)), 0.0) {}
-  // the longest-first items of `times`, in order, on empty slots, until a slot's time reaches `limit`
-  SlotClock(int slots, const std::vector<double>& times, double limit = INFINITY) : SlotClock(slots) {
+  // the longest-first items of `times`, in order, on empty slots
+  SlotClock(int slots, const std::vector<double>& times) : SlotClock(slots) {
     // the first go to a slot each; ascending, they are a heap already
     const size_t n = std::min(times.size(), busy_.size());
     std::reverse_copy(times.begin(), times.begin() + n, busy_.end() - n);
     if (n) longest_ = times[0];
-    for (size_t i = n; i < times.size() && longest_ < limit; ++i) add(times[i]);
+    for (size_t i = n; i < times.size(); ++i) add(times[i]);
   }
   // the next item of `time` goes to the slot that is free first
   void add(double time) {
@@ -164,6 +164,30 @@ class SlotClock {
  private:
   std::vector<double> busy_;
   double longest_ = 0.0;
+};
+
+// The chip under workgroups of one per CU, as its hardware hands them out: in order, in turn over the kNumEngines
+// shader engines (8 XCDs of 4), and a workgroup whose engine has no free CU holds up all behind it.
+class Dispatch {
+ public:
+  Dispatch() : free_(kNumCu, 0.0) {}
+  void add(double time) {
+    constexpr int per = kNumCu / kNumEngines;
+    double* f = &free_[size_t(engine_) * per];          // when the engine's CUs are free, in ascending order
+    engine_ = engine_ + 1 < kNumEngines ? engine_ + 1 : 0;
+    now_ = std::max(now_, f[0]);
+    const double t = now_ + time;
+    longest_ = std::max(longest_, t);
+    int i = 0;
+    for (; i + 1 < per && f[i + 1] < t; ++i) f[i] = f[i + 1];
+    f[i] = t;
+  }
+  double longest() const { return longest_; }
+
+ private:
+  std::vector<double> free_;
+  double now_ = 0.0, longest_ = 0.0;
+  int engine_ = 0;
 };
 
 // Sorts `order` by `key` (key[i] belongs to order[i]), largest first, equal keys in their order: a radix sort over
@@ -349,12 +373,14 @@ struct SplitPlan {
   int64_t pieces = 0;
 };
 
-// Modelled time of a wave of pieces, in tiles: the workgroups are handed out longest first to `slots`
-// that run one at a time, each piece costing its tiles plus `overhead` (queries in, partial out), and
-// every piece of a split item adds its partial rows to the merge.  A plan that cannot beat `best` is not
-// played through.
-double split_cost(const std::vector<int64_t>& ntiles, const SplitPlan& sp, int slots, double overhead, double merge,
-                  double best) {
+// Modelled time of a wave of pieces, in tiles, each costing its tiles plus `overhead` (queries in, partial out);
+// every piece of a split item adds its partial rows to the merge.  The pieces are handed out longest first
+// (Dispatch).  Played as one queue in front of 256 CUs, whole pieces with remainders that fit between them look 5-20 %
+// better than they run: 8 requests of 7K-100K cached and 3-47 new tokens, 128 heads: 294 pieces 1,445 us, 509
+// even ones 1,211.  Over 401 latent waves the plan chosen by this model takes 0.5 % longer than the fastest, by
+// the queue 2.7 %.  A plan that cannot beat `best` is not played through.
+double split_cost(const std::vector<int64_t>& ntiles, const SplitPlan& sp, double overhead, double merge, double best) {
+  const int slots = kNumCu;
   std::vector<uint64_t> len;                 // equal pieces of an item, and its remainder
   std::vector<uint32_t> number;
   len.reserve(2 * ntiles.size());
@@ -376,11 +402,10 @@ double split_cost(const std::vector<int64_t>& ntiles, const SplitPlan& sp, int s
   if (bound >= best) return bound;
   if (count <= slots) return double(most) + overhead + merge * partials;
   sort_descending(len, number);
-  std::vector<double> times;
-  times.reserve(size_t(count));
-  for (size_t i = 0; i < len.size(); ++i) times.insert(times.end(), number[i], double(len[i]) + overhead);
-  const double limit = best - merge * partials, longest = SlotClock(slots, times, limit).longest();
-  return longest < limit ? longest + merge * partials : std::max(best, longest + merge * partials);
+  Dispatch chip;
+  for (size_t i = 0; i < len.size(); ++i)
+    for (uint32_t k = 0; k < number[i] && chip.longest() + merge * partials < best; ++k) chip.add(double(len[i]) + overhead);
+  return chip.longest() + merge * partials;
 }
 
 // Modelled time of a small grouped wave in the 8-wave form (attention and merge, microseconds), its key
@@ -792,10 +817,10 @@ int wavepp_attn_plan(const wavepp_attn_shape* shape, const wavepp_batch* batch, 
     if (mla && longest >= 2 * min_split_tiles) {
       const int slots = kNumCu;
       const double overhead = 5.0, merge = 0.015;
-      double best = split_cost(ntiles, split, slots, overhead, merge, INFINITY);
+      double best = split_cost(ntiles, split, overhead, merge, INFINITY);
       auto consider = [&](SplitPlan sp) {
         if (sp.pieces > fill_target) return;
-        const double c = split_cost(ntiles, sp, slots, overhead, merge, best);
+        const double c = split_cost(ntiles, sp, overhead, merge, best);
         if (c < best) {
           best = c;
           split = std::move(sp);

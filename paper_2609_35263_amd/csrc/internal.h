@@ -12,6 +12,7 @@ constexpr int kGqaRowsPerItem = 256;       // grouped kernel: 8 waves x 32 query
 constexpr int kKvTile = 128;               // grouped kernel: keys per inner-loop tile
 constexpr int kNumCu = 256;                // compute units of the chip: workgroups of a launch that stays resident
 constexpr int kNumXcd = 8;                 // L2 domains a launch is spread over, round-robin
+constexpr int kNumEngines = 32;            // shader engines, which workgroups go to in turn
 constexpr int kMlaRowsPerItem = 128;       // latent kernel: query rows per work item
 constexpr int kMlaKvTile = 64;             // latent kernel: keys per tile
 constexpr int kMergeNarrow = 16;           // merge: splits whose partials one thread loads at once

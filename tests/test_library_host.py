@@ -533,3 +533,34 @@ def test_planning_takes_less_than_a_sort():
 
     plan, sort = best(lambda: wp.plan_for(spec)), best(lambda: np.argsort(x, kind="stable"))
     assert plan < 1.1 * sort, (plan, sort)
+
+
+def _dispatch(times):
+    """When the last of one-per-CU workgroups ends: handed out in order, in turn over 32 shader engines of 8 CUs; one
+    whose engine has no free CU holds up all behind it."""
+    import heapq
+    engines = [[0.0] * 8 for _ in range(32)]
+    now = end = 0.0
+    for i, t in enumerate(times):
+        e = engines[i % 32]
+        now = max(now, e[0])
+        heapq.heapreplace(e, now + t)
+        end = max(end, now + t)
+    return end
+
+
+@pytest.mark.parametrize("heads,prefix,chunk", [
+    (128, [84018, 7174, 87412, 25940, 100000, 40573, 23990, 42278], [6, 15, 11, 4, 7, 47, 3, 17]),
+    (64, [120000, 18227, 24685, 7120, 15793, 100000, 100000, 100000, 50285], [33, 4, 46, 56, 23, 26, 5, 56, 56]),
+    (64, [7620, 478, 296, 290], [35, 125, 26, 529]),
+])
+def test_latent_splits_run_evenly_as_dispatched(heads, prefix, chunk):
+    """The chosen pieces (a piece costs 5 tiles besides its own), handed out longest first the way the hardware does it,
+    end within 1.2 of the even share.  The pieces that one queue in front of 256 CUs would even out best end at 1.25 to
+    1.35 of it."""
+    spec = wl.custom_wave(heads, 1, 576, 512, 64, prefix, chunk, kv_shared=True, seed=3)
+    it = wp.plan_for(spec).items()
+    coverage_check(spec, it, 64)
+    real = it[it[:, 3] > 0]
+    tiles = sorted((-(-(real[:, 5] - real[:, 4]) // 64) + 5).tolist(), reverse=True)
+    assert _dispatch(tiles) <= 1.2 * sum(tiles) / 256
