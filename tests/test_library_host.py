@@ -564,3 +564,24 @@ def test_latent_splits_run_evenly_as_dispatched(heads, prefix, chunk):
     real = it[it[:, 3] > 0]
     tiles = sorted((-(-(real[:, 5] - real[:, 4]) // 64) + 5).tolist(), reverse=True)
     assert _dispatch(tiles) <= 1.2 * sum(tiles) / 256
+
+
+@pytest.mark.parametrize("heads,prefix,chunk,end", [
+    ((64, 8, 128), [8819, 6651, 16440, 13041], [26, 2, 6, 2], 12.5),                                   # by tiles: 13.6
+    ((64, 8, 128), [7468, 31700], [41, 33], 19.5),                                                     # 21.0
+    ((64, 8, 128), [5772, 1217, 4515, 4565, 100001, 38012], [31, 182, 164, 4, 70, 8], 100.0),          # 112.0
+])
+def test_second_round_counts_rows(heads, prefix, chunk, end, monkeypatch):
+    """8-wave items that fill the second round of the CUs in part: handed out in the plan's order, each taking its
+    tiles, half of their time whatever its rows, and one tile more, they end clearly before those placed by tiles."""
+    monkeypatch.delenv("WAVEPP_GQA_WAVES", raising=False)
+    Hq, Hkv, d = heads
+    spec = wl.custom_wave(Hq, Hkv, d, d, 64, prefix, chunk, seed=3)
+    p = wp.plan_for(spec)
+    it = p.items()
+    coverage_check(spec, it, 128)
+    real = it[:, 3] > 0
+    assert p.info()["rows_per_item"] == 256 and 256 < real.sum() <= 512
+    tiles = -(-(it[:, 5] - it[:, 4]) // 128)
+    time = np.where(real, tiles * (0.5 + 0.5 * (-(-it[:, 3] // 32) * 32) / 256) + 1, 0.0)
+    assert _dispatch(time.tolist()) <= end
