@@ -58,17 +58,22 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // looked up once, with scalar loads through the constant address space (the kernel never writes the
 // metadata).  A small wave is a chain of dependent loads (request, page, then the store), so it takes
 // one token per workgroup (launch_append), its request found by one candidate per lane and its row
-// loaded before that: 128 tokens of 8 heads x 128 + 128 took 9 us as 16 workgroups of eight, about 5 us so;
-// 2,048 of 32 heads 16.5 -> 11.6.  Eight tokens are moved in turn, each stored before the next is loaded, so
-// that the workgroups' reads and writes overlap: 8,192 tokens of 8 heads x 128 + 128 in 12.7 us, 5.3 TB/s, with
-// all eight loaded first 14.8; 65,536 of a latent cache 27.4, with that 33.2.
+// loaded before that (EARLY): 128 tokens of 8 heads x 128 + 128 took 9 us as 16 workgroups of eight, about 5 us
+// so; 2,048 of 32 heads 16.5 -> 11.6.  Small waves of eight tokens load all rows early too, a round trip in
+// place of eight: up to 2,560 waves (ten a CU), or 1,792 where a workgroup is four waves.  With more, or with several
+// chunks a thread, each row is stored before the next is loaded, so that the workgroups' reads and writes
+// overlap.  From cold memory, early against in turn: 6,152 tokens of 4 heads x 64 + 64 (769 waves of one) 9.1 /
+// 10.9 us, 16,392 (2,049) 14.9 / 15.2, 32,776 of 2 heads (4,097) 16.4 / 14.6; latent rows, two waves: 8,200 (2,050) 11.9 /
+// 13.1, 16,392 (4,098) 17.5 / 15.4; 8 heads x 128 + 128, four waves: 2,056 tokens (1,028) 10.0 / 13.3, 4,104 (2,052)
+// 14.2 / 13.4; 16 heads, two chunks a thread: 4,104 tokens 33.4 / 23.4.  From warm memory 8,192 tokens of 8 heads
+// take 14.8 / 12.7 us, 65,536 latent rows 33.2 / 27.4.
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ T const_load(const T* ptr) {
   return *((const __attribute__((address_space(4))) T*)(ptr));
 }
 
-template <int DK, int DV, int TOK>
+template <int DK, int DV, int TOK, bool EARLY>
 __global__ __launch_bounds__(256) void append_kernel(DevPlan p, const uint4* __restrict__ k_new,
                                                      const uint4* __restrict__ v_new, uint4* __restrict__ k_pool,
                                                      uint4* __restrict__ v_pool) {
@@ -83,17 +88,21 @@ __global__ __launch_bounds__(256) void append_kernel(DevPlan p, const uint4* __r
     const int h = u / UC, c = u - h * UC;
     return c < KC ? k_new[(t * Hkv + h) * KC + c] : v_new[(t * Hkv + h) * VC + c - KC];
   };
-  uint4 first;
-  if (TOK == 1 && int(threadIdx.x) < per_tok) first = load(t0, threadIdx.x);
+  uint4 first[TOK];
+  if constexpr (EARLY) {
+#pragma unroll
+    for (int i = 0; i < TOK; ++i)
+      if (t0 + i < T && int(threadIdx.x) < per_tok) first[i] = load(t0 + i, threadIdx.x);
+  }
   // request holding token t0: the last r with cu_r <= t0 (requests with no chunk share cu with the next).
-  // For one token, bisection leaves at most 64 candidates, then every lane looks at one.
+  // EARLY: bisection leaves at most 64 candidates, then every lane looks at one.
   int lo = 0, hi = p.num_requests - 1;
-  while (hi - lo >= (TOK == 1 ? 64 : 1)) {
+  while (hi - lo >= (EARLY ? 64 : 1)) {
     const int mid = (lo + hi + 1) >> 1;
     if (const_load(&p.reqs[mid].cu) <= t0) lo = mid; else hi = mid - 1;
   }
   int r = lo;
-  if (TOK == 1 && hi > lo) {
+  if (EARLY && hi > lo) {
     const int mine = lo + int(threadIdx.x & 63);
     r = lo + __popcll(__ballot(mine <= hi && p.reqs[min(mine, hi)].cu <= t0)) - 1;
   }
@@ -109,8 +118,8 @@ __global__ __launch_bounds__(256) void append_kernel(DevPlan p, const uint4* __r
     for (int u = threadIdx.x; u < per_tok; u += blockDim.x) {
       const int h = u / UC;
       const int c = u - h * UC;
-      if constexpr (TOK == 1) {
-        const uint4 x = u == int(threadIdx.x) ? first : load(t, u);
+      if constexpr (EARLY) {
+        const uint4 x = u == int(threadIdx.x) ? first[i] : load(t, u);
         if (c < KC)
           k_pool[((page * Hkv + h) * B + slot) * KC + c] = x;
         else
@@ -1054,19 +1063,24 @@ hipError_t launch_append(const DevPlan& p, const void* k_new, const void* v_new,
                          hipStream_t stream) {
   const int dk = p.head_dim_qk, dv = p.kv_shared ? 0 : p.head_dim_v;
   if (p.total_tokens == 0) return hipSuccess;
-  // one token per workgroup up to 2,048 tokens (fewer than eight workgroups per CU), eight beyond
+  // one token per workgroup up to 2,048 tokens (at most eight workgroups per CU), eight beyond
   const bool few = p.total_tokens <= 2048;
   const int64_t blocks = few ? p.total_tokens : (p.total_tokens + 7) / 8;
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
   const int per_tok = p.num_kv_heads * ((dk + dv) / 8);
   const int threads = std::min(256, (per_tok + 63) / 64 * 64);
+  const bool early = per_tok <= threads && blocks * (threads / 64) <= (threads < 256 ? 10 : 7) * kNumCu;
   auto kn = static_cast<const uint4*>(k_new);
   auto vn = static_cast<const uint4*>(v_new);
   auto kp = static_cast<uint4*>(k_pool);
   auto vp = static_cast<uint4*>(v_pool);
-#define WAVEPP_APPEND(DK_, DV_)                                                                                        \
-  if (few) hipLaunchKernelGGL((append_kernel<DK_, DV_, 1>), dim3(blocks), dim3(threads), 0, stream, p, kn, vn, kp, vp); \
-  else hipLaunchKernelGGL((append_kernel<DK_, DV_, 8>), dim3(blocks), dim3(threads), 0, stream, p, kn, vn, kp, vp);
+#define WAVEPP_APPEND(DK_, DV_)                                                                                       \
+  if (few)                                                                                                            \
+    hipLaunchKernelGGL((append_kernel<DK_, DV_, 1, true>), dim3(blocks), dim3(threads), 0, stream, p, kn, vn, kp, vp); \
+  else if (early)                                                                                                     \
+    hipLaunchKernelGGL((append_kernel<DK_, DV_, 8, true>), dim3(blocks), dim3(threads), 0, stream, p, kn, vn, kp, vp); \
+  else                                                                                                                \
+    hipLaunchKernelGGL((append_kernel<DK_, DV_, 8, false>), dim3(blocks), dim3(threads), 0, stream, p, kn, vn, kp, vp);
   if (dk == 64 && dv == 64) {
     WAVEPP_APPEND(64, 64)
   } else if (dk == 128 && dv == 128) {

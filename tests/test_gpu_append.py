@@ -1,6 +1,7 @@
 """GPU append against the oracle, bit for bit, where the lookup and the launch shape change: one token
-per workgroup up to 2,048 tokens and eight beyond, and waves of more than 64 requests (bisection, then
-one candidate per lane) with idle requests between active ones."""
+per workgroup up to 2,048 tokens and eight beyond, loaded early up to 2,560 waves (20,480 tokens of one wave each) and
+in turn beyond, and waves of more than 64 requests (bisection, then one candidate per lane) with idle requests
+between active ones."""
 import numpy as np
 import pytest
 
@@ -12,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape", [(16, 1, 64, 64), (16, 16, 128, 128), (16, 1, 576, 512)])
-@pytest.mark.parametrize("requests,total", [(1, 1), (64, 65), (65, 100), (200, 2048), (200, 2049), (3, 2055)])
+@pytest.mark.parametrize("requests,total", [(1, 1), (64, 65), (65, 100), (200, 2048), (200, 2049), (3, 2055),
+                                            (200, 20480), (200, 20485)])
 def test_append_matches_oracle(shape, requests, total):
     import torch
     Hq, Hkv, dk, dv = shape

@@ -53,10 +53,14 @@ def test_merge_has_every_partial_in_flight(code, dv):
 
 
 @pytest.mark.parametrize("dims", [(64, 64), (128, 128), (576, 0)])
-def test_append_of_many_tokens_moves_row_by_row(code, dims):
-    """The append of eight tokens a workgroup stores each token's row before it loads the next: with all rows
-    loaded first, the workgroups read together and then write together and keep half of the memory's
-    directions idle."""
-    ins = _find(code, "append_kernel", "ILi%dELi%dELi8E" % dims)
+@pytest.mark.parametrize("early", [False, True])
+def test_append_of_eight_tokens(code, dims, early):
+    """The append of eight tokens a workgroup stores each token's row before it loads the next in waves that fill the
+    chip (with all rows loaded first, the workgroups read together and then write together and keep half of the
+    memory's directions idle), and loads all eight first in smaller ones, which wait for round trips."""
+    ins = _find(code, "append_kernel", "ILi%dELi%dELi8ELb%dE" % (*dims, early))
     moves = [x.split("_")[1] for x in ins if re.match(r"global_(load|store)_dwordx4", x)]
-    assert moves.count("load") >= 8 and ("load", "load") not in zip(moves, moves[1:]), moves
+    if early:
+        assert moves.index("store") >= 8, moves
+    else:
+        assert moves.count("load") >= 8 and ("load", "load") not in zip(moves, moves[1:]), moves
