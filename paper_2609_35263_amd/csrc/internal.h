@@ -116,7 +116,6 @@ struct KdaDevPlan {
   uint32_t serial;
   int32_t num_items;
   int32_t num_heads;
-  int32_t num_slots;
   // 1: the int32 array `list` after the items holds the chains (item * num_heads + head) of each of the kNumCu
   // workgroups, w's from list[list[w]] to list[list[w + 1] - 1].  0: the kernel's fixed order.
   int32_t listed;

@@ -259,7 +259,6 @@ int wavepp_kda_chunked_prefill(const wavepp_kda_plan_t* plan, const void* q, con
   d.serial = plan->serial;
   d.num_items = int32_t(plan->items.size());
   d.num_heads = plan->shape.num_heads;
-  d.num_slots = plan->shape.num_state_slots;
   hipError_t e = launch_kda_prefill(d, q, k, v, alpha, beta, state_pool, out, stream);
   if (e != hipSuccess) return set_hip_error(e, "kda launch");
   return WAVEPP_OK;
