@@ -37,7 +37,7 @@
 //     that same (permuted) order.
 // Every step of either part is a latency chain (LDS round trips, short dependent products), so two
 // waves per SIMD in different parts hide each other's waits.  A wave of 4 x 64 heads x 4,096 tokens:
-// 510 us with four waves that ran the parts in turn, 357-379 us now over boxes, 4.3-4.6 TB/s where a plain copy
+// 510 us with four waves that ran the parts in turn, 357-379 us now over cards, 4.3-4.6 TB/s where a plain copy
 // reached 4.9; with 64 chains on 256 CUs (one 16,384-token request) it is the builders' chain, 10.7 K
 // cycles a block, that bounds it (1,951 -> 1,144 us).  All eight waves in the scaling phase, the P tiles
 // given to the runners, and the next block's loads anywhere but row by row in the scaling phase were
